@@ -123,8 +123,9 @@ typedef struct {
   double easy_axis[3];
 } mmsd_material;
 
-/* Bytes of device memory a problem on this mesh will hold, for admission:
- * exact for the first arena (operators, node state, control), plus an
+/* Bytes of device memory a problem on this mesh will hold, for admission: an
+ * upper bound for the first arena (operators, node state, control; exact but
+ * for the potential matrix's zero couplings, which are not stored), plus an
  * allowance for the multigrid hierarchy, whose size is known only after its
  * setup ((24 + 2 s) bytes per potential-matrix entry and 8 s per potential
  * node, s = 8 for FP64, 4 for mixed). */

@@ -272,6 +272,42 @@ bool dense_inverse(const Csr& A, std::vector<double>& inv) {
 
 }  // namespace
 
+Csr without_zero_couplings(const std::vector<int>& rp, const std::vector<int>& ci, const std::vector<double>& v,
+                           std::vector<double>* diag) {
+  const int n = (int)rp.size() - 1;
+  Csr Z;
+  Z.nrows = Z.ncols = n;
+  Z.rp.assign(n + 1, 0);
+  diag->assign(n, 0.0);
+  std::vector<double>& d = *diag;
+  parallel_for(n, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i)
+      for (int k = rp[i]; k < rp[i + 1]; ++k)
+        if (ci[k] == i) d[i] = v[k];
+  });
+  auto kept = [&](int64_t i, int k) {
+    return ci[k] == i || !(std::fabs(v[k]) <= kZeroCoupling * std::fmin(d[i], d[ci[k]]));
+  };
+  parallel_for(n, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i)
+      for (int k = rp[i]; k < rp[i + 1]; ++k) Z.rp[i + 1] += kept(i, k);
+  });
+  for (int i = 0; i < n; ++i) Z.rp[i + 1] += Z.rp[i];
+  Z.ci.resize(Z.rp[n]);
+  Z.v.resize(Z.rp[n]);
+  parallel_for(n, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i) {
+      int o = Z.rp[i];
+      for (int k = rp[i]; k < rp[i + 1]; ++k)
+        if (kept(i, k)) {
+          Z.ci[o] = ci[k];
+          Z.v[o++] = v[k];
+        }
+    }
+  });
+  return Z;
+}
+
 Csr residual_restriction(const AmgLevel& L) {
   const Csr T = transpose(L.AP);   // (A P)^T: n_next x n
   const Csr& R = L.R;

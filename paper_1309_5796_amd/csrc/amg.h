@@ -60,6 +60,25 @@ void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& f);
 // workers set it to their count of busy workers).  nullptr: no sharing.
 void share_cores(const std::atomic<int>* active);
 
+// A coupling a_ij is as good as zero when |a_ij| <= kZeroCoupling min(a_ii, a_jj):
+// below the rounding error of its own assembled sum, whose terms are of the
+// diagonal's size.
+constexpr double kZeroCoupling = 0x1p-52;
+
+// The matrix (rp, ci, v) without the couplings that are as good as zero; its
+// diagonal in diag.  On a box cut into Kuhn tetrahedra the face and space
+// diagonals carry no coupling (the P1 gradients of their end points are
+// orthogonal, also under the shell's diagonal metric): 6.9 of the 14.6
+// entries per row of the 80 nm cube's potential matrix remain, the others are
+// exact zeros.  The device sweeps and the multigrid setup read the rest
+// only.  Entries keep their order, so with exact zeros every sum has the
+// same bits as before.  The rows of A P shrink from 14.3 to 9.0 entries and
+// those of the next operator from 37.7 to 25.6 with them.  Measured: 14
+// evaluations of the polycrystal 245.1 -> 193.6 ms, four field points of the
+// 80 nm cube 94.0 -> 81.3 ms.
+Csr without_zero_couplings(const std::vector<int>& rp, const std::vector<int>& ci, const std::vector<double>& v,
+                           std::vector<double>* diag);
+
 // M = R (I - A W) with W = wsmooth D^-1: the restriction of the residual left
 // by one damped-Jacobi sweep from zero, b_{l+1} = M b_l.  For symmetric A,
 // R A = (A P)^T, so M = R - (A P)^T W, with the pattern of (A P)^T (which

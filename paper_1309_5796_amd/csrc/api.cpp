@@ -459,7 +459,7 @@ SlicedQ make_sliced_q(const Csr& AP, const Csr& P, int64_t& nnz, bool ordered = 
 template <typename real>
 void bytes_model(mmsd_problem p) {
   const Assembly& A = p->A;
-  const double s = sizeof(real), N = A.N, Nt = A.Nt, zM = (double)A.mci.size(), zL = (double)A.lci.size();
+  const double s = sizeof(real), N = A.N, Nt = A.Nt, zM = (double)A.mci.size(), zL = (double)p->nnzL;
   const double spmvL = 4 * (Nt + 1) + 4 * zL + s * zL;
   double* b = p->btab;
   for (int k = 0; k < kByteSlots; ++k) b[k] = 0;
@@ -766,11 +766,11 @@ constexpr double kStreamBytes = 128.0 * (1 << 20);
 // operators come from the device assembly's buffers (converted on the
 // device); otherwise they are uploaded from the host assembly.
 template <typename real>
-int build_device(mmsd_problem p, const DeviceAssembly* D = nullptr) {
+int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
   mmsd_ctx c = p->ctx;
   const Assembly& A = p->A;
   const int64_t N = A.N, Nt = A.Nt, nnzM = (int64_t)A.mci.size();
-  const int64_t nnzLs = Nt ? sliced_entries(A.lrp) : 0;
+  const int64_t nnzLs = Nt ? sliced_entries(p->L.rp) : 0;
   if (nnzLs >= (int64_t)1 << 31) return invalid("potential matrix too large for 32-bit slice offsets");
   p->lpr = c->lpr;
   p->G = blocks_for(std::max<int64_t>(N, Nt), p->lpr, c->max_blocks);
@@ -808,15 +808,23 @@ int build_device(mmsd_problem p, const DeviceAssembly* D = nullptr) {
       if ((rc = upload_vec<real>(st, base + L.Q[k], A.Q[k]))) return rc;
   }
   if (Nt > 0 && D) {
-    // sliced on the device from the assembled CSR; only the slice offsets
-    // come from the host (the copy of the row starts it keeps)
-    if ((rc = upload_int(st, base + L.lso, slice_offsets(A.lrp)))) return rc;
-    MMSD_HIP(launch_slice_rows<real>(D->lrp, D->lci, D->L, (const int32_t*)(base + L.lso), Nt,
+    // sliced on the device from the assembled CSR; the slice offsets and the
+    // diagonal (which couplings are as good as zero) come from the host
+    double* diag = (double*)c->dalloc(8 * Nt);
+    if (!diag) {
+      set_error("device allocation of the potential matrix's diagonal failed");
+      return MMSD_E_NOMEM;
+    }
+    D->owned.push_back(diag);
+    if ((rc = upload_int(st, base + L.lso, slice_offsets(p->L.rp))) ||
+        (rc = upload_vec<double>(st, (char*)diag, p->Ldiag)))
+      return rc;
+    MMSD_HIP(launch_slice_rows<real>(D->lrp, D->lci, D->L, diag, (const int32_t*)(base + L.lso), Nt,
                                      (int32_t*)(base + L.lsc), (real*)(base + L.lsv), (real*)(base + L.lsum),
                                      (real*)(base + L.rec[0]), (real*)(base + L.rec[1]), st));
   } else if (Nt > 0) {
     // the potential matrix lives on the device only in its sliced layout
-    const Sliced S = make_sliced(A.lrp, A.lci, A.L, (int)Nt);
+    const Sliced S = make_sliced(p->L.rp, p->L.ci, p->L.v, (int)Nt);
     if ((rc = upload_int(st, base + L.lso, S.so)) || (rc = upload_int(st, base + L.lsc, S.sc)) ||
         (rc = upload_vec<real>(st, base + L.lsv, S.sv)))
       return rc;
@@ -1451,19 +1459,16 @@ int mmsd_problem_create(mmsd_ctx c, const mmsd_mesh* mesh, const mmsd_material* 
   }
   const auto t1 = Clock::now();
   if (p->A.Nt > 0) {
-    Csr L0;
-    L0.nrows = L0.ncols = p->A.Nt;
-    L0.rp = p->A.lrp;
-    L0.ci = p->A.lci;
-    L0.v = p->A.L;
-    p->has_amg = amg_setup(std::move(L0), AmgParams{}, &p->amg) && (int)p->amg.lv.size() <= kMaxLevels;
+    p->L = without_zero_couplings(p->A.lrp, p->A.lci, p->A.L, &p->Ldiag);
+    p->nnzL = (int64_t)p->L.ci.size();
+    p->has_amg = amg_setup(p->L, AmgParams{}, &p->amg) && (int)p->amg.lv.size() <= kMaxLevels;
     // the level operators are kept only for sizes and byte counts
   }
   const auto t2 = Clock::now();
   {
     std::lock_guard<std::mutex> lk(c->mu);
     (void)hipSetDevice(c->device);
-    const DeviceAssembly* dp = c->assembly == MMSD_ASSEMBLE_DEVICE ? &D : nullptr;
+    DeviceAssembly* dp = c->assembly == MMSD_ASSEMBLE_DEVICE ? &D : nullptr;
     rc = precision == MMSD_MIXED ? build_device<float>(p, dp) : build_device<double>(p, dp);
     // the build's copies and kernels read D and write the arena: both are
     // released below only once they are done, on failure too
@@ -1471,6 +1476,8 @@ int mmsd_problem_create(mmsd_ctx c, const mmsd_mesh* mesh, const mmsd_material* 
     if (!rc && e != hipSuccess) rc = hip_fail(e, "hipStreamSynchronize");
   }
   D.release(c);
+  p->L = Csr{};
+  p->Ldiag = std::vector<double>();
   if (rc) {
     if (p->arena) c->dfree(p->arena);
     if (p->amg_arena) c->dfree(p->amg_arena);

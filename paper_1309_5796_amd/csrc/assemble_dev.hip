@@ -805,6 +805,7 @@ template <typename real>
 __global__ __launch_bounds__(kAsmBlock) void k_slice_rows(const int32_t* __restrict__ rp,
                                                            const int32_t* __restrict__ ci,
                                                            const double* __restrict__ v,
+                                                           const double* __restrict__ diag,
                                                            const int32_t* __restrict__ so, int64_t n,
                                                            int32_t* __restrict__ sc, real* __restrict__ sv,
                                                            real* __restrict__ lsum, real* __restrict__ rec0,
@@ -816,20 +817,26 @@ __global__ __launch_bounds__(kAsmBlock) void k_slice_rows(const int32_t* __restr
   const int w = (so[sl + 1] - so[sl]) / 64;
   const int a = i < n ? rp[i] : 0, len = i < n ? rp[i + 1] - a : 0;
   const int pad = (int)(i < n - 1 ? i : n - 1);
+  const double di = i < n ? diag[i] : 0.0;
   double sum = 0, dinv = 0;
-  for (int k = 0; k < w; ++k) {
-    const int64_t q = so[sl] + 64LL * k + r;
-    if (k < len) {
-      const int c = ci[a + k];
-      const double x = v[a + k];
+  int o = 0;
+  for (int k = 0; k < len; ++k) {
+    const int c = ci[a + k];
+    const double x = v[a + k];
+    sum += x;
+    if (c == i) dinv = 1.0 / x;
+    else if (fabs(x) <= kZeroCoupling * fmin(di, diag[c])) continue;
+    if (o < w) {   // the host counted the same entries
+      const int64_t q = so[sl] + 64LL * o + r;
       sc[q] = c;
       sv[q] = (real)x;
-      sum += x;
-      if (c == i) dinv = 1.0 / x;
-    } else {
-      sc[q] = pad;
-      sv[q] = (real)0;
     }
+    ++o;
+  }
+  for (; o < w; ++o) {
+    const int64_t q = so[sl] + 64LL * o + r;
+    sc[q] = pad;
+    sv[q] = (real)0;
   }
   if (i < n) {
     lsum[i] = (real)sum;
@@ -848,19 +855,23 @@ hipError_t launch_to_real(const double* src, real* dst, int64_t n, hipStream_t s
 }
 
 template <typename real>
-hipError_t launch_slice_rows(const int32_t* rp, const int32_t* ci, const double* v, const int32_t* so, int64_t n,
-                             int32_t* sc, real* sv, real* lsum, real* rec0, real* rec1, hipStream_t s) {
+hipError_t launch_slice_rows(const int32_t* rp, const int32_t* ci, const double* v, const double* diag,
+                             const int32_t* so, int64_t n, int32_t* sc, real* sv, real* lsum, real* rec0, real* rec1,
+                             hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  k_slice_rows<real><<<grid_of(64 * ((n + 63) / 64)), kAsmBlock, 0, s>>>(rp, ci, v, so, n, sc, sv, lsum, rec0, rec1);
+  k_slice_rows<real><<<grid_of(64 * ((n + 63) / 64)), kAsmBlock, 0, s>>>(rp, ci, v, diag, so, n, sc, sv, lsum, rec0,
+                                                                         rec1);
   return hipGetLastError();
 }
 
 template hipError_t launch_to_real<float>(const double*, float*, int64_t, hipStream_t);
 template hipError_t launch_to_real<double>(const double*, double*, int64_t, hipStream_t);
-template hipError_t launch_slice_rows<float>(const int32_t*, const int32_t*, const double*, const int32_t*, int64_t,
-                                             int32_t*, float*, float*, float*, float*, hipStream_t);
-template hipError_t launch_slice_rows<double>(const int32_t*, const int32_t*, const double*, const int32_t*,
-                                              int64_t, int32_t*, double*, double*, double*, double*, hipStream_t);
+template hipError_t launch_slice_rows<float>(const int32_t*, const int32_t*, const double*, const double*,
+                                             const int32_t*, int64_t, int32_t*, float*, float*, float*, float*,
+                                             hipStream_t);
+template hipError_t launch_slice_rows<double>(const int32_t*, const int32_t*, const double*, const double*,
+                                              const int32_t*, int64_t, int32_t*, double*, double*, double*, double*,
+                                              hipStream_t);
 
 }  // namespace mmsd
 

@@ -55,13 +55,16 @@ int assemble_device_owned(mmsd_ctx_s* c, const mmsd_mesh* mesh, const mmsd_mater
 // FP64 -> real copy of n values (device to device).
 template <typename real>
 hipError_t launch_to_real(const double* src, real* dst, int64_t n, hipStream_t s);
-// CSR (rp, ci, v) of n rows into the 64-row sliced layout with the slice
-// offsets so[(n + 63) / 64 + 1] (every slice as wide as its longest row),
-// plus the FP64 row sums (lsum) and the diagonal's reciprocal in the d field
-// of the two CG record buffers (rec0, rec1: 4 reals per row).
+// CSR (rp, ci, v) of n rows with the diagonal diag, without the couplings
+// that are as good as zero (without_zero_couplings), into the 64-row sliced
+// layout with the slice offsets so[(n + 63) / 64 + 1] (every slice as wide as
+// its longest row), plus the FP64 row sums (lsum) and the diagonal's
+// reciprocal in the d field of the two CG record buffers (rec0, rec1: 4 reals
+// per row).
 template <typename real>
-hipError_t launch_slice_rows(const int32_t* rp, const int32_t* ci, const double* v, const int32_t* so, int64_t n,
-                             int32_t* sc, real* sv, real* lsum, real* rec0, real* rec1, hipStream_t s);
+hipError_t launch_slice_rows(const int32_t* rp, const int32_t* ci, const double* v, const double* diag,
+                             const int32_t* so, int64_t n, int32_t* sc, real* sv, real* lsum, real* rec0, real* rec1,
+                             hipStream_t s);
 
 // Every batch of step launches starts with parity 0 and has an even length,
 // so the state a run is armed with goes into slot 1.
@@ -150,6 +153,9 @@ struct mmsd_problem_s {
   double phase_bytes_h = 0;               // extra FIELD bytes when h is stored
   double prep_bytes_nodemag = 0;
   // multigrid preconditioner of the potential solve
+  mmsd::Csr L;                            // the potential matrix without zero couplings (released after creation)
+  std::vector<double> Ldiag;              // its diagonal (released after creation)
+  int64_t nnzL = 0;                       // its entries
   bool has_amg = false;
   mmsd::AmgHierarchy amg;                 // host copy (sizes; values uploaded)
   std::vector<int64_t> amg_q_nnz;         // entries of each level's fused prolongation/smoothing matrix
