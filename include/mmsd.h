@@ -278,20 +278,19 @@ int mmsd_set_launch_config(mmsd_ctx ctx, int lanes_per_row, int max_blocks);
 
 /* Forms of the multigrid V(1,1) cycle for problems created afterwards on
  * this context (rearrangements of the same cycle, equal up to rounding):
- *   MMSD_VC_FUSE_REST   on coarse levels where the library's cost model
- *                       finds it pays, the restriction runs inside the
- *                       down-sweep's launch, b_{l+1} = R (I - A wd) b;
+ *   MMSD_VC_FUSE_REST   on levels where the library's cost model finds it
+ *                       pays, the down-sweep restricts without forming the
+ *                       residual, b_{l+1} = R (I - A wd) b, and the
+ *                       post-smoothing sweeps A too;
  *   MMSD_VC_FOLD_SOLVE  with the last level fused, the coarsest solve too,
  *                       x_c = Ainv R (I - A wd) b.
- *   MMSD_VC_SLICE_ALL   hold every matrix of the hierarchy (the level
- *                       operators, restrictions and fused prolongation
- *                       matrices) in the 64-row sliced layout and sweep it
+ *   MMSD_VC_SLICE_ALL   sweep every matrix of the hierarchy (the level
+ *                       operators, restrictions and post-smoothing matrices)
  *                       one row per thread, whatever its size and row
- *                       length.  By default only matrices of at least
- *                       65,536 rows and at most 24 entries per row on
- *                       average are sliced, which only meshes of about a
- *                       million nodes reach; the option runs those code
- *                       paths on small meshes (tests).
+ *                       length.  By default only matrices of at least 65,536
+ *                       rows and at most 32 entries per row on average are;
+ *                       the others take 4 to 32 lanes per row.  The option
+ *                       runs those code paths on small meshes (tests).
  * Default: MMSD_VC_FUSE_REST | MMSD_VC_FOLD_SOLVE.  0 gives the plain order
  * (REST and SOLVE launches of their own).  Returns MMSD_E_INVALID for other
  * bits. */

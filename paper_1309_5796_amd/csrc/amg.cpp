@@ -345,6 +345,68 @@ Csr residual_restriction(const AmgLevel& L) {
   return M;
 }
 
+Csr smoothed_prolongation(const AmgLevel& L) {
+  Csr T;
+  T.nrows = L.AP.nrows;
+  T.ncols = L.AP.ncols;
+  T.rp.assign(T.nrows + 1, 0);
+  // rows are the sorted unions of (A P)'s and P's rows: count, then fill
+  auto merge = [&](int i, int* ci, double* v) {
+    int a = L.AP.rp[i], b = L.P.rp[i], o = 0;
+    const int ae = L.AP.rp[i + 1], be = L.P.rp[i + 1];
+    const double w = L.wsmooth * L.dinv[i];
+    while (a < ae || b < be) {
+      const int ca = a < ae ? L.AP.ci[a] : INT32_MAX, cb = b < be ? L.P.ci[b] : INT32_MAX;
+      const int c = std::min(ca, cb);
+      double x = 0;
+      if (cb == c) x += L.P.v[b++];
+      if (ca == c) x -= w * L.AP.v[a++];
+      if (ci) {
+        ci[o] = c;
+        v[o] = x;
+      }
+      ++o;
+    }
+    return o;
+  };
+  parallel_for(T.nrows, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i) T.rp[i + 1] = merge((int)i, nullptr, nullptr);
+  });
+  for (int i = 0; i < T.nrows; ++i) T.rp[i + 1] += T.rp[i];
+  T.ci.resize(T.rp[T.nrows]);
+  T.v.resize(T.rp[T.nrows]);
+  parallel_for(T.nrows, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i) merge((int)i, &T.ci[T.rp[i]], &T.v[T.rp[i]]);
+  });
+  return T;
+}
+
+Csr fused_post_smoothing(const AmgLevel& L, const Csr& T) {
+  const int n = L.A.nrows;
+  Csr C;
+  C.nrows = n;
+  C.ncols = n + T.ncols;
+  C.rp.resize(n + 1);
+  for (int i = 0; i <= n; ++i) C.rp[i] = L.A.rp[i] + T.rp[i];
+  C.ci.resize(C.rp[n]);
+  C.v.resize(C.rp[n]);
+  parallel_for(n, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i) {
+      int o = C.rp[i];
+      const double w = L.wsmooth * L.dinv[i];
+      for (int k = L.A.rp[i]; k < L.A.rp[i + 1]; ++k, ++o) {
+        C.ci[o] = L.A.ci[k];
+        C.v[o] = (L.A.ci[k] == i ? 2.0 : 0.0) - w * L.A.v[k];
+      }
+      for (int k = T.rp[i]; k < T.rp[i + 1]; ++k, ++o) {
+        C.ci[o] = n + T.ci[k];
+        C.v[o] = T.v[k];
+      }
+    }
+  });
+  return C;
+}
+
 bool amg_setup(Csr A0, const AmgParams& prm, AmgHierarchy* h) {
   h->lv.clear();
   const double nnz0 = (double)A0.ci.size();

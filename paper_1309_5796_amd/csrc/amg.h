@@ -85,6 +85,16 @@ Csr without_zero_couplings(const std::vector<int>& rp, const std::vector<int>& c
 // holds R's, A's diagonal being stored); rows with ascending columns.
 Csr residual_restriction(const AmgLevel& L);
 
+// T = (I - W A) P, W = wsmooth D^-1: what the post-smoothing adds per coarse
+// value, x = W b + W (b - A W b) + T x_{l+1}.  For symmetric A, T = M^T.  Rows
+// with ascending columns, the union of the patterns of A P and P.
+Csr smoothed_prolongation(const AmgLevel& L);
+
+// [2 I - W A | T] (T the smoothed_prolongation): the pre-smoothing, its
+// residual and the post-smoothing in one matrix over [W b | x_{l+1}], since
+// W b + W (b - A W b) = 2 W b - W A (W b).  Columns of T are shifted by n.
+Csr fused_post_smoothing(const AmgLevel& L, const Csr& T);
+
 // Build the hierarchy for the symmetric positive definite CSR matrix A
 // (taken by value: pass a moved copy to spare one).  Returns false (and
 // leaves h empty) when the matrix does not coarsen.

@@ -118,126 +118,64 @@ Prob<real>& desc_of(mmsd_problem p) {
   return *reinterpret_cast<Prob<real>*>(p->desc);
 }
 
-// Lanes per row W (4, 8, 16 or 32) for a multigrid matrix swept in CSR.  A
-// block pass covers 512 / W rows; a lane loads 8 entries per batch (4 with
-// 4 lanes).  Rows of more than 16 entries on average take 8 lanes (64
-// entries per batch), more than 64 take 16, shorter ones 4.  A small matrix
-// whose rows all fit one pass of the 512 blocks of a full-GPU launch at 32
-// lanes (at most 8192 rows) takes 32 lanes when its rows are long: that
-// spreads its few rows over many more blocks, and a row of up to 256
-// entries is one batch.  The coarse levels are latency-bound (each sweep a
-// chain of dependent loads): measured 1-1.5 us faster per sweep than 8
-// lanes.
-constexpr int64_t kSmallRows = 512 * (kBlock / 32);
-int row_lanes(const Csr& M) {
-  const double avg = M.nrows ? (double)M.ci.size() / M.nrows : 0.0;
-  if (avg > 16 && M.nrows <= kSmallRows) return 32;
-  return avg > 64 ? 16 : avg > 16 ? 8 : 4;
-}
-// Block passes of a CSR sweep of n rows at W lanes per row over g blocks.
+// Block passes of a sweep of n rows at W lanes per row over g blocks.
 static int64_t sweep_passes(int64_t n, int64_t g, int W) {
   const int64_t rpp = kBlock / W, c = (n + g - 1) / g;
   return (c + rpp - 1) / rpp;
 }
 
-// Latency cost of a sweep of matrix M (rows of avg entries) at W lanes per
-// row (W = 1: sliced, one thread per row) over g blocks, in units of one
-// dependent round trip: each block pass loads the row start, then per batch
-// the entries and their gathers (8 entries per lane per batch at 8 or more
-// lanes, 4 otherwise), then stores.
-static int64_t sweep_cost(int64_t n, double avg, int64_t g, int W) {
-  const double per_batch = W == 1 ? 4.0 : W == 4 ? 16.0 : 8.0 * W;
-  const int64_t batches = std::max<int64_t>(1, (int64_t)std::ceil(avg / per_batch));
-  return sweep_passes(n, g, W) * (batches + 1);
+// Latency cost of a sweep of n rows of avg entries at W lanes per row over a
+// full launch's 512 blocks, in units of one dependent round trip: each block
+// pass loads the slice's offset, then per batch the entries and their gathers
+// (8 steps per batch), then stores.
+static int64_t sweep_cost(int64_t n, double avg, int W) {
+  const int64_t batches = std::max<int64_t>(1, (int64_t)std::ceil(avg / (8.0 * W)));
+  return sweep_passes(n, 512, W) * (batches + 1);
 }
 
-// Lanes per row of a CSR sweep: the default's (row_lanes) unless 4 or 8
-// lanes cost fewer round trips over a full launch's 512 blocks (the 39k-row
-// level of the 80 nm cube, rows of ~20 entries: one block pass at 4 lanes
-// against two at 8).
-static int model_lanes(const Csr& R) {
-  const double avg = R.nrows ? (double)R.ci.size() / R.nrows : 0.0;
-  int best = row_lanes(R);
-  int64_t cost = sweep_cost(R.nrows, avg, 512, best);
-  for (int W : {4, 8}) {
-    const int64_t c = sweep_cost(R.nrows, avg, 512, W);
-    if (c < cost) {
-      cost = c;
-      best = W;
-    }
-  }
+// Lanes per row of a multigrid matrix: many rows take one thread each (enough
+// wavefronts to fill the GPU); else the lanes with the fewest round trips, on
+// ties the fewest, whose loads carry the most entries.
+// One row per thread up to 32 entries per row on average: the polycrystal's
+// 323k-row level (rows of 27 entries) in slices of 4 lanes made 14
+// evaluations 183 instead of 166 ms.
+constexpr int kThreadRows = 65536;
+constexpr double kThreadRow = 32;
+static int row_lanes(int64_t n, double avg) {
+  if (n >= kThreadRows && avg <= kThreadRow) return 1;
+  int best = 4;
+  for (int W : {8, 16, 32})
+    if (sweep_cost(n, avg, W) < sweep_cost(n, avg, best)) best = W;
   return best;
 }
 
-// Shape of a DOWN launch that also restricts (levels >= 1), for the 512
-// blocks of a full-GPU launch: the split of the blocks between A's rows (nA
-// rows of avgA entries at wa lanes) and M's, and M's lanes per row, that
-// minimize the slower part's cost (on ties: the most blocks for M, then
-// the cheapest M sweep; measured 1-1.5 us faster on the coarse levels than
-// the fewest).  The fusion is kept (m_blocks > 0) when
-// that cost is below the two separate sweeps' plus one launch (counted as
-// 2 round trips): on coarse, latency-bound levels it removes a launch; on a
-// large level, M (about 5x R's entries) would cost more than it saves.
-static void fused_shape(int64_t nA, double avgA, int wa, int64_t nR, double avgR, int wr, const Csr& M, int& wm,
-                        int& m_blocks) {
-  const double avgM = M.nrows ? (double)M.ci.size() / M.nrows : 0.0;
-  const int64_t separate = sweep_cost(nA, avgA, 512, wa) + sweep_cost(nR, avgR, 512, wr) + 2;
-  int64_t best = INT64_MAX;
-  wm = 4;
-  m_blocks = 0;
-  int64_t best_m = INT64_MAX;
-  for (int64_t gd = 8; gd <= 504; gd += 8) {   // ties: the largest share for M, then M's cheapest lanes
-    const int64_t ca = sweep_cost(nA, avgA, gd, wa);
-    for (int W : {4, 8, 16, 32}) {
-      const int64_t cm = sweep_cost(M.nrows, avgM, 512 - gd, W), c = std::max(ca, cm);
-      if (c < best || (c == best && 512 - gd > m_blocks) || (c == best && 512 - gd == m_blocks && cm < best_m)) {
-        best = c;
-        best_m = cm;
-        wm = W;
-        m_blocks = (int)(512 - gd);
-      }
-    }
-  }
-  if (best >= separate) m_blocks = 0;
-}
-
-// Shape of the last DOWN when it also forms the coarsest solution (Ainv M
-// folded in): the dense rows of Ainv M take one block each per pass (the
-// whole block streams a row), so the split of the 512 blocks and A's lanes
-// per row are chosen together for the fewest round trips of the slower
-// part (on ties: the most blocks for the dense rows).  On the 80 nm cube
-// this gives each of the 384 dense rows a block of its own, A at 16 lanes.
-static void folded_shape(int64_t nA, double avgA, int64_t nc, int& wa, int& m_blocks) {
-  int64_t best = INT64_MAX;
-  for (int64_t gd = 8; gd <= 504; gd += 8) {
-    const int64_t gm = 512 - gd, cm = 2 * ((nc + gm - 1) / gm);
-    for (int W : {4, 8, 16, 32}) {
-      const int64_t c = std::max(sweep_cost(nA, avgA, gd, W), cm);
-      if (c < best || (c == best && gm > m_blocks)) {
-        best = c;
-        wa = W;
-        m_blocks = (int)gm;
-      }
-    }
-  }
+// Whether a level's DOWN restricts with M = R (I - A wd) (nR rows of avgM
+// entries; A's sweep then moves into POST, where it shares a launch with T's)
+// or leaves the residual for a REST operation with R (avgR entries).  M saves
+// a launch (about 2 round trips) and the residual's way through memory but
+// has about 3 (finest level) to 6 times R's entries, so the cost of a sweep
+// is the larger of its round trips over a full launch's 512 blocks and its
+// bytes, a round trip being worth about 3.5 MB at the rate a sweep of large
+// matrices reaches.  On the finest level that draws the line near 150,000
+// rows: with M the 20 nm cube's iteration loses one of six launches, while
+// the 80 nm cube's grows from 67.1 to 70.0 us (PCG_B with M 18.5 us against
+// 10.1 + 9.0 us for PCG_B and REST, POST with A 14.0 against 11.1 us).
+constexpr double kTripBytes = 3.5e6;
+static bool fuse_restriction(int64_t n, int64_t nR, double avgR, double avgM, size_t s) {
+  auto cost = [&](double avg) {
+    return std::max((double)sweep_cost(nR, avg, row_lanes(nR, avg)), (4 + s) * avg * (double)nR / kTripBytes);
+  };
+  return cost(avgM) < cost(avgR) + 2 + 2.0 * s * n / kTripBytes;
 }
 
 // Largest dense Ainv M (coarsest size x last level's rows) folded into the
 // last DOWN.
 constexpr double kMaxFoldedBytes = 64.0 * (1 << 20);
 
-// Average row length up to which a matrix with many rows is sliced.
-constexpr size_t kWideRow = 24;
-// Rows from which a multigrid matrix with short rows (at most kWideRow on
-// average) is held in the sliced layout (no CSR copy) and swept one row per
-// thread (enough wavefronts to fill the GPU); long rows keep their lanes per
-// row (row_lanes), which measured faster.
-constexpr int kSlicedRows = 65536;
-
-// 64-row sliced layout of a CSR matrix: slice s holds rows 64s..64s+63,
-// entry k of row i at so[s] + 64 k + (i mod 64); short rows are padded with
-// their own column (clamped to the column range) and a zero value.  Entry
-// k's value is v[stride k + off] (one value of an interleaved array).
+// A CSR matrix in slices of one wavefront, W lanes per row (1: 64 rows per
+// slice): slice s starts at so[s] and is as wide as its longest row; entry k
+// of its row r is at so[s] + 64 (k / W) + r W + k mod W; the rest is padded
+// with the row's own column (clamped to the column range) and a zero value.
 // Slices are built in parallel.
 struct Sliced {
   std::vector<int> so, sc;
@@ -265,16 +203,15 @@ std::vector<int> window_order(const std::vector<int>& len) {
   });
   return order;
 }
-// Offsets of the 64-row slices of a CSR pattern: slice s starts at so[s]
-// and holds 64 x (its longest row) entries.
-std::vector<int> slice_offsets(const std::vector<int>& rp) {
-  const int64_t n = (int64_t)rp.size() - 1, ns = (n + 63) / 64;
+// Offsets of the slices of a CSR pattern (W lanes per row).
+std::vector<int> slice_offsets(const std::vector<int>& rp, int W = 1) {
+  const int64_t n = (int64_t)rp.size() - 1, rows = 64 / W, ns = (n + rows - 1) / rows;
   std::vector<int> so(ns + 1, 0);
   parallel_for(ns, [&](int64_t a, int64_t b) {
     for (int64_t sl = a; sl < b; ++sl) {
       int w = 0;
-      for (int64_t i = 64 * sl; i < std::min<int64_t>(n, 64 * sl + 64); ++i) w = std::max(w, rp[i + 1] - rp[i]);
-      so[sl + 1] = 64 * w;
+      for (int64_t i = rows * sl; i < std::min<int64_t>(n, rows * (sl + 1)); ++i) w = std::max(w, rp[i + 1] - rp[i]);
+      so[sl + 1] = 64 * ((w + W - 1) / W);
     }
   });
   for (int64_t sl = 0; sl < ns; ++sl) so[sl + 1] += so[sl];
@@ -282,8 +219,8 @@ std::vector<int> slice_offsets(const std::vector<int>& rp) {
 }
 
 Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci, const std::vector<double>& v,
-                   int ncols, int stride = 1, int off = 0, bool ordered = false) {
-  const int64_t n = (int64_t)rp.size() - 1, ns = (n + 63) / 64;
+                   int ncols, int W = 1, bool ordered = false) {
+  const int64_t n = (int64_t)rp.size() - 1, rows = 64 / W, ns = (n + rows - 1) / rows;
   Sliced S;
   if (ordered) {
     std::vector<int> len(n);
@@ -291,162 +228,28 @@ Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci, const
     S.order = window_order(len);
     std::vector<int> rpo(n + 1, 0);   // row starts of the rows in position order (lengths only matter)
     for (int64_t q = 0; q < n; ++q) rpo[q + 1] = rpo[q] + len[S.order[q]];
-    S.so = slice_offsets(rpo);
+    S.so = slice_offsets(rpo, W);
   } else {
-    S.so = slice_offsets(rp);
+    S.so = slice_offsets(rp, W);
   }
   S.sc.assign(S.so[ns], 0);
   S.sv.assign(S.so[ns], 0.0);
   parallel_for(ns, [&](int64_t a, int64_t b) {
     for (int64_t sl = a; sl < b; ++sl) {
       const int w = (S.so[sl + 1] - S.so[sl]) / 64;
-      for (int r = 0; r < 64; ++r) {
-        const int64_t pos = 64 * sl + r;
+      for (int r = 0; r < rows; ++r) {
+        const int64_t pos = rows * sl + r;
         const int64_t i = pos < n && ordered ? S.order[pos] : pos;
         const int len = pos < n ? rp[i + 1] - rp[i] : 0;
-        for (int k = 0; k < w; ++k) {
-          const int64_t q = S.so[sl] + 64LL * k + r;
+        for (int k = 0; k < w * W; ++k) {
+          const int64_t q = S.so[sl] + 64LL * (k / W) + r * W + k % W;
           if (k < len) {
             S.sc[q] = ci[rp[i] + k];
-            S.sv[q] = v[(size_t)stride * (rp[i] + k) + off];
+            S.sv[q] = v[rp[i] + k];
           } else {
             S.sc[q] = (int)std::min<int64_t>(i, ncols - 1);
           }
         }
-      }
-    }
-  });
-  return S;
-}
-
-// The matrix the fused prolongation and post-smoothing sweeps: the union of
-// the patterns of A P and P (P's lies inside A P's when A's diagonal is
-// stored) with the value pairs {(A P)_ik, P_ik}, two values per entry in v.
-// Each row lists P's columns first (front[i] of them, P's whole row), then
-// the others, each part by ascending column.  Rows are built in parallel.
-Csr fused_q(const Csr& AP, const Csr& P, std::vector<int>& front) {
-  Csr Q;
-  const int n = AP.nrows;
-  Q.nrows = n;
-  Q.ncols = AP.ncols;
-  Q.rp.assign(n + 1, 0);
-  front.assign(n, 0);
-  // row lengths: |AP row| + P columns missing from it (rows sorted by column)
-  parallel_for(n, [&](int64_t a0, int64_t b0) {
-    for (int64_t i = a0; i < b0; ++i) {
-      int a = AP.rp[i], extra = 0;
-      for (int b = P.rp[i]; b < P.rp[i + 1]; ++b) {
-        while (a < AP.rp[i + 1] && AP.ci[a] < P.ci[b]) ++a;
-        if (a == AP.rp[i + 1] || AP.ci[a] != P.ci[b]) ++extra;
-      }
-      Q.rp[i + 1] = AP.rp[i + 1] - AP.rp[i] + extra;
-      front[i] = P.rp[i + 1] - P.rp[i];
-    }
-  });
-  for (int i = 0; i < n; ++i) Q.rp[i + 1] += Q.rp[i];
-  Q.ci.resize(Q.rp[n]);
-  Q.v.resize(2 * (size_t)Q.rp[n]);
-  parallel_for(n, [&](int64_t a0, int64_t b0) {
-    for (int64_t i = a0; i < b0; ++i) {
-      int o = Q.rp[i];
-      // P's columns, with the (A P) value where A P has the column
-      int a = AP.rp[i];
-      for (int b = P.rp[i]; b < P.rp[i + 1]; ++b, ++o) {
-        while (a < AP.rp[i + 1] && AP.ci[a] < P.ci[b]) ++a;
-        Q.ci[o] = P.ci[b];
-        Q.v[2 * (size_t)o] = (a < AP.rp[i + 1] && AP.ci[a] == P.ci[b]) ? AP.v[a] : 0.0;
-        Q.v[2 * (size_t)o + 1] = P.v[b];
-      }
-      // then A P's other columns
-      int b = P.rp[i];
-      for (a = AP.rp[i]; a < AP.rp[i + 1]; ++a) {
-        while (b < P.rp[i + 1] && P.ci[b] < AP.ci[a]) ++b;
-        if (b < P.rp[i + 1] && P.ci[b] == AP.ci[a]) continue;
-        Q.ci[o] = AP.ci[a];
-        Q.v[2 * (size_t)o] = AP.v[a];
-        Q.v[2 * (size_t)o + 1] = 0.0;
-        ++o;
-      }
-    }
-  });
-  return Q;
-}
-
-// The sliced form of Q, built from A P and P directly: the (A P) values over
-// Q's pattern (rows ordered as in fused_q: P's columns first), and the P
-// values of the row fronts as a sliced matrix of their own (same 64-row
-// slices, entry k of row i at po[s] + 64 k + i mod 64, zero-padded).
-// nnz receives Q's entry count.  Slices are built in parallel.
-struct SlicedQ {
-  Sliced ap;
-  std::vector<int> po;
-  std::vector<double> pv;
-};
-SlicedQ make_sliced_q(const Csr& AP, const Csr& P, int64_t& nnz, bool ordered = false) {
-  const int64_t n = AP.nrows, ns = (n + 63) / 64;
-  std::vector<int> len(n), front(n);
-  parallel_for(n, [&](int64_t a0, int64_t b0) {
-    for (int64_t i = a0; i < b0; ++i) {
-      int a = AP.rp[i], extra = 0;
-      for (int b = P.rp[i]; b < P.rp[i + 1]; ++b) {
-        while (a < AP.rp[i + 1] && AP.ci[a] < P.ci[b]) ++a;
-        if (a == AP.rp[i + 1] || AP.ci[a] != P.ci[b]) ++extra;
-      }
-      len[i] = AP.rp[i + 1] - AP.rp[i] + extra;
-      front[i] = P.rp[i + 1] - P.rp[i];
-    }
-  });
-  nnz = 0;
-  for (int64_t i = 0; i < n; ++i) nnz += len[i];
-  SlicedQ S;
-  if (ordered) S.ap.order = window_order(len);
-  auto row_of = [&](int64_t pos) { return ordered ? (int64_t)S.ap.order[pos] : pos; };
-  S.ap.so.assign(ns + 1, 0);
-  S.po.assign(ns + 1, 0);
-  parallel_for(ns, [&](int64_t a, int64_t b) {
-    for (int64_t sl = a; sl < b; ++sl) {
-      int w = 0, wp = 0;
-      for (int64_t q = 64 * sl; q < std::min<int64_t>(n, 64 * sl + 64); ++q) {
-        w = std::max(w, len[row_of(q)]);
-        wp = std::max(wp, front[row_of(q)]);
-      }
-      S.ap.so[sl + 1] = 64 * w;
-      S.po[sl + 1] = 64 * wp;
-    }
-  });
-  for (int64_t sl = 0; sl < ns; ++sl) {
-    S.ap.so[sl + 1] += S.ap.so[sl];
-    S.po[sl + 1] += S.po[sl];
-  }
-  S.ap.sc.assign(S.ap.so[ns], 0);
-  S.ap.sv.assign(S.ap.so[ns], 0.0);
-  S.pv.assign(S.po[ns], 0.0);
-  parallel_for(ns, [&](int64_t a0, int64_t b0) {
-    for (int64_t sl = a0; sl < b0; ++sl) {
-      const int w = (S.ap.so[sl + 1] - S.ap.so[sl]) / 64;
-      for (int r = 0; r < 64; ++r) {
-        const int64_t pos = 64 * sl + r;
-        const int64_t i = pos < n ? row_of(pos) : pos;
-        auto at = [&](int k) { return S.ap.so[sl] + 64LL * k + r; };
-        int k = 0;
-        if (pos < n) {
-          int a = AP.rp[i];
-          for (int b = P.rp[i]; b < P.rp[i + 1]; ++b, ++k) {   // P's columns
-            while (a < AP.rp[i + 1] && AP.ci[a] < P.ci[b]) ++a;
-            S.ap.sc[at(k)] = P.ci[b];
-            S.ap.sv[at(k)] = (a < AP.rp[i + 1] && AP.ci[a] == P.ci[b]) ? AP.v[a] : 0.0;
-            S.pv[S.po[sl] + 64LL * k + r] = P.v[b];
-          }
-          int b = P.rp[i];
-          for (a = AP.rp[i]; a < AP.rp[i + 1]; ++a) {   // A P's other columns
-            while (b < P.rp[i + 1] && P.ci[b] < AP.ci[a]) ++b;
-            if (b < P.rp[i + 1] && P.ci[b] == AP.ci[a]) continue;
-            S.ap.sc[at(k)] = AP.ci[a];
-            S.ap.sv[at(k)] = AP.v[a];
-            ++k;
-          }
-        }
-        for (; k < w; ++k) S.ap.sc[at(k)] = (int)std::min<int64_t>(i, AP.ncols - 1);   // padding
       }
     }
   });
@@ -479,20 +282,23 @@ void bytes_model(mmsd_problem p) {
       const double n = L.A.nrows, nn = L.P.ncols;
       const double zA = (double)L.A.ci.size(), zP = (double)L.P.ci.size(), zQ = (double)p->amg_q_nnz[l];
       const double spA = 4 * (n + 1) + (4 + s) * zA, spR = 4 * (nn + 1) + (4 + s) * zP;
-      // Q: CSR with value pairs, or sliced with the (A P) values and P's
-      // values of the row fronts
-      const double spQ = p->amg_q_sliced[l] ? 4 * (n + 1) + (4 + s) * zQ + s * (double)L.P.ci.size()
-                                            : 4 * (n + 1) + (4 + 2 * s) * zQ;
-      b[byte_slot(PH_MG, MG_DOWN, (int)l)] = spA + 3 * s * n;     // b, wd in; res out
-      b[byte_slot(PH_MG, MG_REST, (int)l)] = spR + s * n + s * nn;   // res in; b out
-      if (l + 1 < H.lv.size()) b[byte_slot(PH_MG, MG_REST, (int)l)] += 2 * s * nn;   // wd in; wd b out
-      if (p->amg_folded && l + 1 == H.lv.size())   // DOWN also solves: dense Ainv M rows, x_c out
-        b[byte_slot(PH_MG, MG_DOWN, (int)l)] += s * nn * n + s * nn;
-      else if (p->amg_m_nnz[l] > 0)   // DOWN also restricts: M rows, b_{l+1} out (and wd in, wd b out)
-        b[byte_slot(PH_MG, MG_DOWN, (int)l)] += 4 * (nn + 1) + (4 + s) * (double)p->amg_m_nnz[l] + s * nn +
-                                               (l + 1 < H.lv.size() ? 2 * s * nn : 0.0);
-      b[byte_slot(PH_MG, MG_POST, (int)l)] = spQ + s * nn + 4 * s * n;   // x_{l+1}, b, wd, res in; xb out
-      if (l == 0) b[byte_slot(PH_MG, MG_POST, 0)] += 2 * s * n;     // p carried over into the {z, p} records
+      const double spQ = 4 * (n + 1) + (4 + s) * zQ;
+      const bool last = l + 1 == H.lv.size(), fused = p->amg_m_nnz[l] > 0;
+      const double next = s * nn + (last ? 0.0 : 2 * s * nn);   // b_{l+1} out (and wd in, wd b out)
+      const double spM = 4 * (nn + 1) + (4 + s) * (double)p->amg_m_nnz[l];
+      double* down = &b[byte_slot(PH_MG, MG_DOWN, (int)l)];
+      if (fused && last && p->amg_folded) *down = s * nn * n + s * n + s * nn;   // dense Ainv M rows, b in; x_c out
+      else if (fused) *down = spM + s * n + next + (l == 0 ? 2 * s * n : 0.0);   // M, b in (level 0: wd in, wd r out)
+      else *down = spA + 3 * s * n;                                             // b, wd in; res out
+      b[byte_slot(PH_MG, MG_REST, (int)l)] = spR + s * n + next;                // res in
+      // x_{l+1}, and b, wd, res in or (fused) wd b; xb out
+      b[byte_slot(PH_MG, MG_POST, (int)l)] = spQ + s * nn + (fused ? 2 : 4) * s * n;
+      if (l == 0) b[byte_slot(PH_MG, MG_POST, 0)] += (fused ? 3 : 2) * s * n;   // p carried over into {z, p} (and r in)
+    }
+    if (p->amg_m_nnz[0] > 0) {
+      b[PH_PCG_A] = spmvL + 5 * s * Nt;   // {z, p}, r in; {r, q} out
+      // {r, q}, {z, p}, u, wd in; {z, p}, r, u, wd r out; M and b_1
+      b[PH_PCG_B] = 11 * s * Nt + b[byte_slot(PH_MG, MG_DOWN, 0)] - 3 * s * Nt;
     }
     b[byte_slot(PH_MG, MG_SOLVE, 0)] = s * (double)H.nc * (H.nc + 2);
   }
@@ -518,65 +324,50 @@ int build_amg(mmsd_problem p) {
     off.push_back(at);
     return at;
   };
-  struct LvOff { size_t arp, aci, av, wd, qrp, qci, qv, qpo, qpv, rrp, rci, rv, mrp, mci, mv, b, wb, res, xb, sl[3][4]; };
+  struct LvOff { size_t wd, b, wb, res, sl[3][4]; };
   std::vector<LvOff> lo(nl);
-  // the fused prolongation / post-smoothing matrices (two values per entry),
-  // and on levels >= 1 the restriction M = R (I - A wd) that DOWN sweeps too
-  std::vector<Csr> Q(nl), M(nl);
-  std::vector<std::vector<int>> qfront(nl);
-  std::vector<SlicedQ> sq(nl);
-  // every matrix sliced, as on the largest meshes (a context option for tests)
+  // every matrix one row per thread (a context option for tests)
   const bool slice_all = (c->vcycle & MMSD_VC_SLICE_ALL) != 0;
+  auto lanes_of = [&](const Csr& X) {
+    return slice_all ? 1 : row_lanes(X.nrows, (double)X.ci.size() / std::max(1, X.nrows));
+  };
+  // per level: fused or not, and the slices of the matrices it sweeps in DOWN
+  // (A, unfused; level 0's is the potential matrix), POST (Q) and REST or
+  // DOWN (R or M)
+  std::vector<std::array<Sliced, 3>> sl(nl);
+  std::vector<std::array<int, 3>> lanes(nl, {1, 1, 1});
+  std::vector<int> fused(nl, 0);
+  Csr M;   // the last level's, for the folded solve
   p->amg_q_nnz.assign(nl, 0);
   p->amg_m_nnz.assign(nl, 0);
-  p->amg_q_sliced.assign(nl, 0);
   for (int l = 0; l < nl; ++l) {
     const AmgLevel& L = H.lv[l];
-    // Q's rows average about A P's entries: sliced by the same rule as A, R
-    const bool q_sliced = slice_all || (L.AP.nrows >= kSlicedRows && L.AP.ci.size() <= kWideRow * (size_t)L.AP.nrows);
-    if (q_sliced) {
-      sq[l] = make_sliced_q(L.AP, L.P, p->amg_q_nnz[l], /*ordered=*/true);
-      p->amg_q_sliced[l] = 1;
-    } else {
-      Q[l] = fused_q(L.AP, L.P, qfront[l]);
-      p->amg_q_nnz[l] = (int64_t)Q[l].ci.size();
+    Csr Q = smoothed_prolongation(L);
+    const double nn = std::max(1, L.P.ncols);
+    fused[l] = (c->vcycle & MMSD_VC_FUSE_REST) &&
+               fuse_restriction(L.A.nrows, L.P.ncols, L.P.ci.size() / nn, Q.ci.size() / nn, s);
+    if (fused[l]) {
+      M = residual_restriction(L);
+      Q = fused_post_smoothing(L, Q);
+      p->amg_m_nnz[l] = (int64_t)M.ci.size();
     }
-    if (l >= 1) M[l] = residual_restriction(L);
-  }
-  // sliced copies (A of levels >= 1, Q, R) of the matrices with many rows
-  std::vector<std::array<Sliced, 3>> sl(nl);
-  for (int l = 0; l < nl; ++l) {
-    const AmgLevel& L = H.lv[l];
-    const Csr* M[3] = {&L.A, nullptr, &L.R};
+    p->amg_q_nnz[l] = (int64_t)Q.ci.size();
+    const Csr* X[3] = {fused[l] || l == 0 ? nullptr : &L.A, &Q, fused[l] ? &M : &L.R};
     for (int k = 0; k < 3; ++k) {
-      if (k == 1) {   // Q: sliced above when its level qualifies
-        if (!p->amg_q_sliced[l]) continue;
-        sl[l][1] = std::move(sq[l].ap);
-      } else {
-        if ((k == 0 && l == 0) ||
-            (!slice_all && (M[k]->nrows < kSlicedRows || M[k]->ci.size() > kWideRow * (size_t)M[k]->nrows)))
-          continue;
-        sl[l][k] = make_sliced(M[k]->rp, M[k]->ci, M[k]->v, M[k]->ncols, 1, 0, /*ordered=*/true);
-      }
+      if (!X[k]) continue;
+      lanes[l][k] = lanes_of(*X[k]);
+      if (X[k]->ci.size() >= (size_t)1 << 29) return invalid("multigrid matrix too large to slice");
+      sl[l][k] = make_sliced(X[k]->rp, X[k]->ci, X[k]->v, X[k]->ncols, lanes[l][k], /*ordered=*/true);
       if ((int64_t)sl[l][k].so.back() >= (int64_t)1 << 30) return invalid("multigrid matrix too large to slice");
     }
-  }
-  // which levels' DOWN also restricts, and how
-  std::vector<int> wm(nl, 4), mblk(nl, 0);
-  for (int l = 1; l < nl && (c->vcycle & MMSD_VC_FUSE_REST); ++l) {
-    const AmgLevel& L = H.lv[l];
-    fused_shape(L.A.nrows, (double)L.A.ci.size() / L.A.nrows, sl[l][0].so.empty() ? model_lanes(L.A) : 1, L.R.nrows,
-                (double)L.R.ci.size() / std::max(1, L.R.nrows), sl[l][2].so.empty() ? model_lanes(L.R) : 1, M[l], wm[l],
-                mblk[l]);
   }
   // the last level's DOWN also solves the coarsest level when it restricts
   // and the dense product Ainv M is small: x_c = (Ainv M) b
   std::vector<double> ainv_m;
   p->amg_folded = false;
-  int wa_last = 0;   // A's lanes on the last level when the solve is folded (0: the default)
-  if ((c->vcycle & MMSD_VC_FOLD_SOLVE) && nl >= 2 && mblk[nl - 1] > 0 &&
+  if ((c->vcycle & MMSD_VC_FOLD_SOLVE) && nl >= 2 && fused[nl - 1] &&
       (double)H.nc * H.lv[nl - 1].A.nrows * s <= kMaxFoldedBytes) {
-    const Csr& Ml = M[nl - 1];
+    const Csr& Ml = M;
     const int64_t nlast = H.lv[nl - 1].A.nrows;
     ainv_m.assign((size_t)H.nc * nlast, 0.0);
     parallel_for(H.nc, [&](int64_t I0, int64_t I1) {
@@ -589,13 +380,7 @@ int build_amg(mmsd_problem p) {
       }
     });
     p->amg_folded = true;
-    const AmgLevel& Ll = H.lv[nl - 1];
-    if (sl[nl - 1][0].so.empty())
-      folded_shape(Ll.A.nrows, (double)Ll.A.ci.size() / Ll.A.nrows, H.nc, wa_last, mblk[nl - 1]);
-  }
-  for (int l = 1; l < nl; ++l) {
-    if (mblk[l] > 0 && !(p->amg_folded && l == nl - 1)) p->amg_m_nnz[l] = (int64_t)M[l].ci.size();
-    else if (mblk[l] == 0) M[l] = Csr{};
+    sl[nl - 1][2] = Sliced{};   // M itself is not swept then
   }
   for (int l = 0; l < nl; ++l) {
     const AmgLevel& L = H.lv[l];
@@ -608,37 +393,12 @@ int build_amg(mmsd_problem p) {
       lo[l].sl[k][2] = take(s * S.sv.size());
       lo[l].sl[k][3] = take(4 * S.order.size());
     }
-    // CSR copies only of the matrices without a sliced one
-    if (l > 0 && sl[l][0].so.empty()) {
-      lo[l].arp = take(4 * (n + 1));
-      lo[l].aci = take(4 * L.A.ci.size());
-      lo[l].av = take(s * L.A.ci.size());
-    }
-    if (sl[l][1].so.empty()) {
-      lo[l].qrp = take(4 * (n + 1));
-      lo[l].qci = take(4 * Q[l].ci.size());
-      lo[l].qv = take(2 * s * Q[l].ci.size());
-    } else {
-      lo[l].qpo = take(4 * sq[l].po.size());
-      lo[l].qpv = take(s * sq[l].pv.size());
-    }
-    if (sl[l][2].so.empty()) {
-      lo[l].rrp = take(4 * (nn + 1));
-      lo[l].rci = take(4 * L.R.ci.size());
-      lo[l].rv = take(s * L.R.ci.size());
-    }
-    if (mblk[l] > 0) {
-      lo[l].mrp = take(4 * (nn + 1));
-      lo[l].mci = take(4 * M[l].ci.size());
-      lo[l].mv = take(s * M[l].ci.size());
-    }
     lo[l].wd = take(s * n);
     lo[l].b = take(s * n);
-    lo[l].wb = take(s * n);
+    lo[l].wb = take(s * (n + nn));   // [wd b | the next level's result], which a fused POST gathers as one vector
     lo[l].res = take(s * n);
-    lo[l].xb = take(s * n);
   }
-  const size_t o_ainv = take(s * (size_t)H.nc * H.nc), o_bc = take(s * H.nc), o_xc = take(s * H.nc);
+  const size_t o_ainv = take(s * (size_t)H.nc * H.nc), o_bc = take(s * H.nc);
   const size_t o_ainvm = take(s * ainv_m.size());
   size_t o_r2[2];
   for (int k = 0; k < 2; ++k) o_r2[k] = take(s * Nt);
@@ -660,22 +420,6 @@ int build_amg(mmsd_problem p) {
     const AmgLevel& L = H.lv[l];
     std::vector<double> wd(L.dinv.size());
     for (size_t i = 0; i < wd.size(); ++i) wd[i] = L.wsmooth * L.dinv[i];
-    const bool csr[3] = {l > 0 && sl[l][0].so.empty(), sl[l][1].so.empty(), sl[l][2].so.empty()};
-    if (csr[0] && ((rc = upload_int(st, base + lo[l].arp, L.A.rp)) || (rc = upload_int(st, base + lo[l].aci, L.A.ci)) ||
-                   (rc = upload_vec<real>(st, base + lo[l].av, L.A.v))))
-      return rc;
-    if (csr[1] && ((rc = upload_int(st, base + lo[l].qrp, Q[l].rp)) || (rc = upload_int(st, base + lo[l].qci, Q[l].ci)) ||
-                   (rc = upload_vec<real>(st, base + lo[l].qv, Q[l].v))))
-      return rc;
-    if (!csr[1] &&
-        ((rc = upload_int(st, base + lo[l].qpo, sq[l].po)) || (rc = upload_vec<real>(st, base + lo[l].qpv, sq[l].pv))))
-      return rc;
-    if (csr[2] && ((rc = upload_int(st, base + lo[l].rrp, L.R.rp)) || (rc = upload_int(st, base + lo[l].rci, L.R.ci)) ||
-                   (rc = upload_vec<real>(st, base + lo[l].rv, L.R.v))))
-      return rc;
-    if (mblk[l] > 0 && ((rc = upload_int(st, base + lo[l].mrp, M[l].rp)) || (rc = upload_int(st, base + lo[l].mci, M[l].ci)) ||
-                   (rc = upload_vec<real>(st, base + lo[l].mv, M[l].v))))
-      return rc;
     if ((rc = upload_vec<real>(st, base + lo[l].wd, wd))) return rc;
     const int* so[3] = {nullptr, nullptr, nullptr};
     const int* sc[3] = {nullptr, nullptr, nullptr};
@@ -705,8 +449,6 @@ int build_amg(mmsd_problem p) {
     d.qso = so[1];
     d.qsc = sc[1];
     d.qsv = sv[1];
-    d.qpo = csr[1] ? nullptr : (const int*)(base + lo[l].qpo);
-    d.qpv = csr[1] ? nullptr : (const real*)(base + lo[l].qpv);
     d.rso = so[2];
     d.rsc = sc[2];
     d.rsv = sv[2];
@@ -715,28 +457,16 @@ int build_amg(mmsd_problem p) {
     d.rord = sp[2];
     d.n = L.A.nrows;
     d.n_next = L.P.ncols;
-    d.lanes_a = (l == nl - 1 && wa_last) ? wa_last : model_lanes(L.A);
-    d.lanes_q = model_lanes(Q[l]);
-    d.lanes_r = model_lanes(L.R);
-    d.lanes_m = wm[l];
-    d.m_blocks = mblk[l];
-    d.mrp = mblk[l] > 0 ? (const int*)(base + lo[l].mrp) : nullptr;
-    d.mci = mblk[l] > 0 ? (const int*)(base + lo[l].mci) : nullptr;
-    d.mv = mblk[l] > 0 ? (const real*)(base + lo[l].mv) : nullptr;
-    d.arp = csr[0] ? (const int*)(base + lo[l].arp) : nullptr;
-    d.aci = csr[0] ? (const int*)(base + lo[l].aci) : nullptr;
-    d.av = csr[0] ? (const real*)(base + lo[l].av) : nullptr;
-    d.qrp = csr[1] ? (const int*)(base + lo[l].qrp) : nullptr;
-    d.qci = csr[1] ? (const int*)(base + lo[l].qci) : nullptr;
-    d.qv = csr[1] ? (const Pair<real>*)(base + lo[l].qv) : nullptr;
-    d.rrp = csr[2] ? (const int*)(base + lo[l].rrp) : nullptr;
-    d.rci = csr[2] ? (const int*)(base + lo[l].rci) : nullptr;
-    d.rv = csr[2] ? (const real*)(base + lo[l].rv) : nullptr;
+    d.lanes_a = std::ilogb(lanes[l][0]);
+    d.lanes_q = std::ilogb(lanes[l][1]);
+    d.lanes_r = std::ilogb(lanes[l][2]);
+    d.fused = fused[l];
     d.wd = (const real*)(base + lo[l].wd);
     d.b = (real*)(base + lo[l].b);
     d.wb = (real*)(base + lo[l].wb);
+    d.xn = d.wb + d.n;
     d.res = (real*)(base + lo[l].res);
-    d.xb = (real*)(base + lo[l].xb);
+    d.xb = l > 0 ? lv[l - 1].xn : nullptr;
   }
   if ((rc = upload_vec<real>(st, base + o_ainv, H.Ainv))) return rc;
   if ((rc = upload_vec<real>(st, base + o_ainvm, ainv_m))) return rc;
@@ -744,13 +474,13 @@ int build_amg(mmsd_problem p) {
   MMSD_HIP(hipStreamSynchronize(st));
   P.n_lev = nl;
   P.mg_fused = 0;
-  for (int l = 0; l < nl; ++l) P.mg_fused |= (lv[l].m_blocks > 0) << l;
+  for (int l = 0; l < nl; ++l) P.mg_fused |= lv[l].fused << l;
   P.nc = H.nc;
   P.lev = (const MgLevel<real>*)(base + o_lev);
   P.Ainv = (const real*)(base + o_ainv);
   P.AinvM = p->amg_folded ? (const real*)(base + o_ainvm) : nullptr;
   P.bc = (real*)(base + o_bc);
-  P.xc = (real*)(base + o_xc);
+  P.xc = lv[nl - 1].xn;
   for (int k = 0; k < 2; ++k) {
     P.r2[k] = (real*)(base + o_r2[k]);
   }

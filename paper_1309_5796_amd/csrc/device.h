@@ -18,7 +18,7 @@
 //          (eq. (10)).
 // With the multigrid preconditioner the potential solve runs PH_MG
 // operations (one V-cycle operation on one level per launch; a DOWN may
-// also restrict, and on the last level also solve the coarsest level),
+// restrict, and on the last level solve the coarsest level),
 // PH_PCG_A and PH_PCG_B instead of CG0 / CG.
 //
 // Launches alternate a parity bit.  A launch of parity p reads the control
@@ -42,10 +42,9 @@ enum Phase : int {
   PH_IDLE = 0, PH_PREP = 1, PH_CG0 = 2, PH_CG = 3, PH_FIELD = 4, PH_DONE = 5, PH_START = 6,
   PH_MG = 7,     // one multigrid V-cycle operation (sub-op and level in Ctrl)
   PH_PCG_A = 8,  // AMG-preconditioned CG: p = z + beta p, q = L p, p.q
-  PH_PCG_B = 9   // u += alpha p, r -= alpha q, and the finest pre-smoothing residual
+  PH_PCG_B = 9   // u += alpha p, r -= alpha q, and the finest level's DOWN of the next cycle
 };
-enum MgOp : int { MG_DOWN = 0, MG_REST = 1, MG_SOLVE = 2, MG_POST = 3,
-                  MG_RESTM = 4 };   // inside a DOWN launch: the blocks that sweep M
+enum MgOp : int { MG_DOWN = 0, MG_REST = 1, MG_SOLVE = 2, MG_POST = 3 };
 enum Precond : int { PC_AUTO = 0, PC_JACOBI = 1, PC_AMG = 2 };
 constexpr int kMaxLevels = 12;
 enum Stage : int { ST_INIT = 0, ST_RUN = 1, ST_EVAL = 2 };
@@ -132,46 +131,38 @@ using DevRef = __attribute__((address_space(1))) T&;
 template <typename real, template <typename> class Ptr>
 struct MgLevelT {
   int n, n_next;
-  int lanes_a, lanes_q, lanes_r, lanes_m;   // lanes per row for A, Q, R, M in CSR: 4, 8, 16 or 32
-  int m_blocks;            // blocks of 512 (scaled to the launch's) that sweep M in DOWN; 0: no M,
-                           // the level restricts in a REST operation of its own
-  int pad;
-  Ptr<const int> arp;
-  Ptr<const int> aci;
-  Ptr<const real> av;
+  int lanes_a, lanes_q, lanes_r;   // log2 of the lanes per row of A, Q and R or M: 0 or 2 to 5
+  int fused;               // 1: DOWN restricts with M alone and POST sweeps A with Q (one matrix);
+                           // 0: DOWN leaves the residual, a REST operation restricts it with R
   Ptr<const real> wd;
-  Ptr<const int> qrp;          // Q: n x n_next, the pattern of A P with value pairs {(A P)_ik, P_ik}
-  Ptr<const int> qci;
-  Ptr<const Pair<real>> qv;
-  Ptr<const int> rrp;          // R = P^T: n_next x n
-  Ptr<const int> rci;
-  Ptr<const real> rv;
-  Ptr<const int> mrp;          // M = R (I - A wd): n_next x n, b_{l+1} = M b
-  Ptr<const int> mci;
-  Ptr<const real> mv;
-  // sliced copies (64-row slices, as the potential matrix) of A, Q and R;
-  // null when the matrix has too few rows to fill the GPU one row per thread
+  // The matrices, each in slices of one wavefront (64 / lanes rows): the
+  // slices' offsets, columns, values and the row at each position (rows are
+  // sorted by length inside windows, which cuts the slices' padding; null:
+  // position = row).  Entry k of the slice's row r is at step k / lanes of
+  // lane r lanes + k mod lanes.
+  // A: of an unfused level (level 0: the potential matrix)
   Ptr<const int> aso;
   Ptr<const int> asc;
   Ptr<const real> asv;
-  Ptr<const int> qso;          // Q sliced: the (A P) values; P's values of the row
-  Ptr<const int> qsc;          // fronts (each row lists P's columns first) in
-  Ptr<const real> qsv;         // slices of their own (offsets qpo)
-  Ptr<const int> qpo;
-  Ptr<const real> qpv;
+  Ptr<const int> aord;
+  // Q: unfused, T = (I - wd A) P (n x n_next); fused, [2 wd - wd A wd | T] with the
+  // wd on the right inside the gathered vector: columns j < n gather wb[j],
+  // the others x_{l+1}[j - n], which lies right behind wb
+  Ptr<const int> qso;
+  Ptr<const int> qsc;
+  Ptr<const real> qsv;
+  Ptr<const int> qord;
+  // R = P^T of an unfused level (n_next x n), or M = R (I - A wd) of a fused
+  // one, b_{l+1} = M b
   Ptr<const int> rso;
   Ptr<const int> rsc;
   Ptr<const real> rsv;
-  // sliced rows are held in a windowed order (rows sorted by length inside
-  // windows of 512, which cuts the slices' padding): the row at each
-  // position of A's, Q's and R's sliced copies (null: position = row)
-  Ptr<const int> aord;
-  Ptr<const int> qord;
   Ptr<const int> rord;
   Ptr<real> b;                 // right-hand side (level 0 uses the CG residual)
-  Ptr<real> wb;                // wd b (levels >= 1), written with b
-  Ptr<real> res;               // residual after pre-smoothing
-  Ptr<real> xb;                // after post-smoothing (level 0: the preconditioned residual z)
+  Ptr<real> wb;                // wd b, written with b (level 0: wd r, on a fused level)
+  Ptr<real> res;               // residual after pre-smoothing (unfused levels)
+  Ptr<real> xn;                // the next level's (or the coarsest) result, right behind wb
+  Ptr<real> xb;                // after post-smoothing: the previous level's xn (level 0: z in the {z, p} records)
 };
 
 // Per-node state of the potential solve, packed so that one gathered
@@ -220,7 +211,7 @@ struct ProbT {
   Ptr<Rec<real>> rec[2];      // CG state by buffer parity (pcur)
   // multigrid-preconditioned CG (absent when n_lev == 0)
   int n_lev;              // levels with a coarser level below them
-  int mg_fused;           // bit l: level l's DOWN also restricts (MgLevel::m_blocks > 0)
+  int mg_fused;           // bit l: level l's DOWN restricts (MgLevel::fused)
   int nc;                 // size of the coarsest level
   Ptr<const MgLevelT<real, Ptr>> lev;
   Ptr<const real> Ainv;       // dense inverse of the coarsest operator, row-major nc x nc
@@ -230,8 +221,8 @@ struct ProbT {
   Ptr<real> xc;
   Ptr<real> r2[2];            // residual by parity (rcur)
   Ptr<Pair<real>> zp;         // {z, p}: preconditioned residual and search direction
-  Ptr<Pair<real>> rq;         // {wd r, wd q} of the current iteration
-  Ptr<real> q;                // L p
+  Ptr<Pair<real>> rq;         // of the current iteration: {r, q} (level 0 fused) or {wd r, wd q}
+  Ptr<real> q;                // L p (level 0 unfused)
   Ptr<const double> btab;     // algorithmic bytes per executed phase, indexed by byte_slot()
   // reductions and control
   Ptr<unsigned> ndone;        // nullable: incremented once when the problem finishes

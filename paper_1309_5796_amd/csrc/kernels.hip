@@ -2,14 +2,13 @@
 //
 // One launch advances every unfinished problem of a table by one phase (see
 // device.h for the phases and the parity protocol).  Work layout:
-//  * Rows of the potential matrix (and of multigrid matrices with many short
-//    rows) are swept one per thread from a 64-row sliced layout: a wavefront
-//    owns a slice, so index and value loads are contiguous 64-wide accesses.
-//  * Other CSR rows (magnet matrices, coarse multigrid levels) are split over
-//    `LPR` lanes (4, 8 or 16) of a 64-wide wavefront.  A block of 512 threads
-//    walks a contiguous chunk of rows in passes.  Node vectors are gathered
-//    (they stay in L2: every entry is reused by ~15 rows); values gathered
-//    together are packed into records.
+//  * The matrices of the potential solve are swept from slices of one
+//    wavefront, 64 rows of one lane each or fewer rows of 4 to 32 lanes, so
+//    that index and value loads are contiguous 64-wide accesses.
+//  * The magnet matrices' CSR rows are split over `LPR` lanes (4, 8 or 16) of a
+//    64-wide wavefront.  A block of 512 threads walks its rows in passes.
+//    Node vectors are gathered (they stay in L2: every entry is reused by
+//    several rows); values gathered together are packed into records.
 //  * Blocks are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8);
 //    the row chunks are cut into 8 contiguous runs, one per XCD, so that
 //    neighbour gathers stay inside an XCD's own L2 and every XCD gets an
@@ -130,13 +129,11 @@ __device__ __forceinline__ void cayley(real mx, real my, real mz, real Hx, real 
   }
 }
 
-// Row loops load kUnroll column indices per lane first, then issue all the
+// Row loops load several column indices per lane first, then issue all the
 // gathers, then accumulate: two dependent memory round trips per row batch
-// instead of two per nonzero.
-constexpr int kUnroll = 4;
-// The FIELD phase gathers four values per neighbour (m and u) and takes half
-// the batch in FP64 to bound its register use (the kernel's VGPR count is
-// the largest phase's).
+// instead of two per nonzero.  The FIELD phase gathers four values per
+// neighbour (m and u) and takes half the batch in FP64 to bound its register
+// use (the kernel's VGPR count is the largest phase's).
 template <typename real>
 constexpr int kUnrollWide = sizeof(real) == 8 ? 2 : 4;
 
@@ -171,40 +168,35 @@ __device__ __forceinline__ void st(DevPtr<Rec<real>> p, int i, const Rec<real>& 
 
 // Rows of block `blk` (of G, a multiple of 8) for R rows, as passes of
 // `rpp` rows starting at r0, r0 + rs, ... below r1 (row i of a pass is valid
-// when i < r1).  The rows are cut into chunks of ceil(R / G) rounded up to
-// `align` (64 for the sliced layout, whose wavefronts each own one slice),
-// and to whole passes when a chunk takes more than one, so a small level
-// spreads over up to G blocks.  The chunks are dealt to the 8 XCDs (block b
-// runs on XCD b % 8) as 8 contiguous runs of almost equal length: each XCD
-// sweeps neighbouring rows, which keeps their gathers in its own L2, and all
-// 8 XCDs share the work also when there are fewer chunks than blocks.  When
-// a chunk takes several passes, the blocks of an XCD take the passes of the
-// XCD's run in turn (block k the passes k, k + n, k + 2n, ... of its n
-// blocks) instead of one contiguous chunk each: the XCD then sweeps its run
-// as one front of n passes, so a row's neighbours a grid plane away (tens
-// of thousands of rows on the largest meshes) were just loaded by the front
-// and are still in the L2 when they are gathered.
+// when i < r1).  The rows are cut into 8 contiguous runs of almost equal
+// length, one per XCD (block b runs on XCD b % 8): each XCD sweeps
+// neighbouring rows, which keeps their gathers in its own L2.  When a chunk
+// of ceil(R / G) rows, rounded up to `align` (64 for the sliced layout, whose
+// wavefronts each own one slice), fits one pass, every block takes one such
+// chunk, so a small level spreads over up to G blocks.  Otherwise the blocks
+// of an XCD take the passes of the XCD's run in turn (block k the passes k,
+// k + n, k + 2n, ... of its n blocks): the XCD sweeps its run as one front of
+// n passes, so a row's neighbours a grid plane away (tens of thousands of
+// rows on the largest meshes) were just loaded by the front and are still in
+// the L2 when they are gathered.  All blocks take part (chunks of whole passes
+// left 8% of the blocks idle on the polycrystal's finest level and 38% on its
+// 323k-row level: 14 evaluations 181.3 -> 171.9 ms).
 __device__ __forceinline__ void chunk_rows(int R, int G, int blk, int rpp, int align, int& r0, int& r1, int& rs) {
   r0 = r1 = R;
   rs = rpp;
   if (R <= 0) return;
   long long c = ((long long)R + G - 1) / G;
   c = (c + align - 1) / align * align;
-  if (c > rpp) c = (c + rpp - 1) / rpp * rpp;
-  const int nch = (int)((R + c - 1) / c);          // <= G
+  const bool one = c <= rpp;   // one pass: the block's own chunk
+  if (!one) c = rpp;
+  const int nch = (int)((R + c - 1) / c);
   const int x = blk & 7, k = blk >> 3;
-  const int s = x * nch / 8, e = (x + 1) * nch / 8;
+  const int s = (int)((long long)x * nch / 8), e = (int)((long long)(x + 1) * nch / 8);
   if (k >= e - s) return;
-  if (c <= rpp) {   // one pass: the block's own chunk
-    const long long a = (long long)(s + k) * c;
-    r0 = (int)a;
-    r1 = (int)(a + c < R ? a + c : R);
-    return;
-  }
-  const long long a = (long long)s * c, b = (long long)e * c;
-  r0 = (int)(a + (long long)k * rpp);
+  const long long a = (s + k) * c, b = one ? a + c : e * c;
+  r0 = (int)a;
   r1 = (int)(b < R ? b : R);
-  rs = (e - s) * rpp;
+  if (!one) rs = (G >> 3) * rpp;
 }
 
 // Matrix entries of the sliced sweeps are read once per sweep.  On problems
@@ -218,94 +210,85 @@ __device__ __forceinline__ T stream_ld(DevPtr<const T> p, int i) {
   else return p[i];
 }
 
-// Rows of the potential matrix are swept one per thread from its 64-row
-// sliced layout: a wavefront owns one slice, so every index and value load
-// is one contiguous 64-wide access, and a whole block-pass covers 512 rows.
-constexpr int kSellU = 4;   // entries per thread loaded before their gathers
+// The matrices of the potential solve are held in slices: a wavefront owns a
+// slice of 64 / W rows with W = 2^lw lanes per row, so that every index and
+// value load is one contiguous 64-wide access whatever the row length (W = 1:
+// one row per thread, for many rows).  Entry k of the slice's row r is at
+// step k / W of lane r W + k mod W; a slice is as wide as its longest row.
+// The sweeps of small levels are bound by their chain of loads and by issuing
+// them; against CSR rows of W lanes (whose loads touch 64 / W separate row
+// pieces, and which the longer rows of the large meshes kept), an evaluation
+// of the 20 nm cube took 1.08 instead of 1.18 ms, 14 evaluations of the
+// polycrystal 163.8 instead of 171.7 ms.
 
-// sum_k v[k] * g(column k) over row i of a matrix in the sliced layout
-// (slice offsets so, columns sc, values sv).  The calling wavefront's active
-// lanes all lie in one slice.
-template <typename real, bool NT, typename G>
-__device__ __forceinline__ real sell_row_t(DevPtr<const int> so, DevPtr<const int> sc, DevPtr<const real> sv, int i,
-                                           G&& g) {
-  const int sl = __builtin_amdgcn_readfirstlane(i >> 6);
+// U steps from step k0 of a slice that is w steps wide: indices and values
+// first, then all the gathers, then the products.
+template <typename real, int U, bool NT, typename Acc, typename G>
+__device__ __forceinline__ void slice_steps(DevPtr<const int> sc, DevPtr<const real> sv, int o, int k0, int w, Acc& acc,
+                                            G&& g) {
+  int j[U];
+  real v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const bool ok = k0 + u < w;
+    const int q = o + 64 * (ok ? k0 + u : 0);
+    j[u] = stream_ld<NT>(sc, q);
+    v[u] = ok ? stream_ld<NT>(sv, q) : real(0);
+  }
+  real x[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) x[u] = g(j[u]);
+#pragma unroll
+  for (int u = 0; u < U; ++u) acc += (Acc)v[u] * x[u];
+}
+
+// The calling lane's part of sum_k v[k] * g(column k) over the row at
+// position i of a matrix in slices (offsets so, columns sc, values sv); the
+// row's sum is the group sum over its W lanes.  The calling wavefront's
+// active lanes all lie in one slice.  Sums are kept in Acc.  A remainder of
+// up to 4 steps takes a batch of its own: steps beyond the slice's width
+// would still issue their loads.
+template <typename real, bool NT, typename Acc, typename G>
+__device__ __forceinline__ Acc slice_row_t(DevPtr<const int> so, DevPtr<const int> sc, DevPtr<const real> sv, int i,
+                                           int lw, G&& g) {
+  const int sl = __builtin_amdgcn_readfirstlane(i >> (6 - lw));
   const int o0 = so[sl];
   const int w = (so[sl + 1] - o0) >> 6;
-  const int o = o0 + (i & 63);
-  real acc = 0;
-  for (int k0 = 0; k0 < w; k0 += kSellU) {
-    int j[kSellU];
-    real v[kSellU];
-#pragma unroll
-    for (int u = 0; u < kSellU; ++u) {
-      const bool ok = k0 + u < w;
-      const int q = o + 64 * (ok ? k0 + u : 0);
-      j[u] = stream_ld<NT>(sc, q);
-      v[u] = ok ? stream_ld<NT>(sv, q) : real(0);
-    }
-    real x[kSellU];
-#pragma unroll
-    for (int u = 0; u < kSellU; ++u) x[u] = g(j[u]);
-#pragma unroll
-    for (int u = 0; u < kSellU; ++u) acc += v[u] * x[u];
-  }
+  const int o = o0 + (threadIdx.x & 63);
+  Acc acc = 0;
+  int k0 = 0;
+  for (; k0 + 4 < w; k0 += 8) slice_steps<real, 8, NT>(sc, sv, o, k0, w, acc, g);
+  if (k0 < w) slice_steps<real, 4, NT>(sc, sv, o, k0, w, acc, g);
   return acc;
 }
 
-// Row i of the sliced fused matrix Q: {sum (A P)_ik g(k), sum P_ik g(k)}
-// from one gather per entry; P's values cover the first wp entries of the
-// row (sliced with offsets po), the (A P) values all of them.
-template <typename real, bool NT, typename G>
-__device__ __forceinline__ Pair<real> sell_row_q_t(DevPtr<const int> so, DevPtr<const int> sc, DevPtr<const real> sv,
-                                                   DevPtr<const int> po, DevPtr<const real> pv, int i, G&& g) {
-  const int sl = __builtin_amdgcn_readfirstlane(i >> 6);
-  const int o0 = so[sl], p0 = po[sl];
-  const int w = (so[sl + 1] - o0) >> 6, wp = (po[sl + 1] - p0) >> 6;
-  const int o = o0 + (i & 63), op = p0 + (i & 63);
-  real sa = 0, sb = 0;
-  for (int k0 = 0; k0 < w; k0 += kSellU) {
-    int j[kSellU];
-    real va[kSellU], vb[kSellU];
-#pragma unroll
-    for (int u = 0; u < kSellU; ++u) {
-      const int k = k0 + u;
-      const bool ok = k < w;
-      const int q = o + 64 * (ok ? k : 0);
-      j[u] = stream_ld<NT>(sc, q);
-      va[u] = ok ? stream_ld<NT>(sv, q) : real(0);
-      vb[u] = k < wp ? stream_ld<NT>(pv, op + 64 * k) : real(0);
-    }
-    real x[kSellU];
-#pragma unroll
-    for (int u = 0; u < kSellU; ++u) x[u] = g(j[u]);
-#pragma unroll
-    for (int u = 0; u < kSellU; ++u) {
-      sa += va[u] * x[u];
-      sb += vb[u] * x[u];
-    }
-  }
-  return Pair<real>{sa, sb};
+// ... with the problem's load form (a uniform branch: both loops are
+// compiled, one runs).
+template <typename real, typename Acc = real, typename G>
+__device__ __forceinline__ Acc slice_row(DevPtr<const int> so, DevPtr<const int> sc, DevPtr<const real> sv, int i,
+                                         int lw, bool nt, G&& g) {
+  return nt ? slice_row_t<real, true, Acc>(so, sc, sv, i, lw, g) : slice_row_t<real, false, Acc>(so, sc, sv, i, lw, g);
 }
 
-// The sliced sweeps with the problem's load form (a uniform branch: both
-// loops are compiled, one runs).
-template <typename real, typename G>
-__device__ __forceinline__ real sell_row(DevPtr<const int> so, DevPtr<const int> sc, DevPtr<const real> sv, int i,
-                                         bool nt, G&& g) {
-  return nt ? sell_row_t<real, true>(so, sc, sv, i, g) : sell_row_t<real, false>(so, sc, sv, i, g);
-}
-template <typename real, typename G>
-__device__ __forceinline__ Pair<real> sell_row_q(DevPtr<const int> so, DevPtr<const int> sc, DevPtr<const real> sv,
-                                                 DevPtr<const int> po, DevPtr<const real> pv, int i, bool nt,
-                                                 G&& g) {
-  return nt ? sell_row_q_t<real, true>(so, sc, sv, po, pv, i, g) : sell_row_q_t<real, false>(so, sc, sv, po, pv, i, g);
+// Sum over the 2^lw lanes (1, 4, 8, 16 or 32) of a row.
+template <typename T>
+__device__ __forceinline__ T lanes_sum(T v, int lw) {
+  if (lw == 0) return v;
+  v = group_sum<T, 4>(v);
+  if (lw > 2) v += xl::dpp<xl::kHalfMirror>(v);
+  if (lw > 3) v += xl::dpp<xl::kMirror>(v);
+  if (lw > 4) {
+    T a, b;
+    xl::swap_pair<16>(v, a, b);
+    v = a + b;
+  }
+  return v;
 }
 
 // ... over row i of the potential matrix
-template <typename real, typename G>
-__device__ __forceinline__ real sell_sum(const ProbDev<real>& P, int i, G&& g) {
-  return sell_row<real>(P.lso, P.lsc, P.lsv, i, P.stream != 0, g);
+template <typename real, typename Acc = real, typename G>
+__device__ __forceinline__ Acc l_row(const ProbDev<real>& P, int i, G&& g) {
+  return slice_row<real, Acc>(P.lso, P.lsc, P.lsv, i, 0, P.stream != 0, g);
 }
 
 // ---- PREP: trial magnetization, Poisson right-hand side, initial residual ----
@@ -339,7 +322,7 @@ __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, doubl
   for (int base = pass; base < pass + kBlock && base < m1; base += RPP) {
     const int i = base + slot;
     const bool valid = i < m1;
-    real bi = 0;
+    double bi = 0;
     if (valid) {
       if (lane == 0) {
         real ox, oy, oz;
@@ -354,15 +337,15 @@ __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, doubl
           const int j = P.mci[k];
           real ox, oy, oz;
           cayley<real>(max_[j], may[j], maz[j], Hax[j], Hay[j], Haz[j], ht, ox, oy, oz);
-          bi += P.D1[0][k] * ox + P.D1[1][k] * oy + P.D1[2][k] * oz;
+          bi += (double)P.D1[0][k] * ox + (double)P.D1[1][k] * oy + (double)P.D1[2][k] * oz;
         }
       }
     }
     if (demag) {
-      bi = group_sum<real, LPR>(bi);
+      bi = group_sum<double, LPR>(bi);
       if (valid && lane == 0) {
-        if (amg) r2[i] = bi;
-        else rec[i].r = bi;
+        if (amg) r2[i] = real(bi);
+        else rec[i].r = real(bi);
       }
     }
   }
@@ -388,13 +371,17 @@ __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, doubl
     // FP32: the potential is large and smooth next to its residual, and the
     // rounding of the matrix values times u would swamp b - L u; L's rows sum
     // to zero away from the Dirichlet boundary, so the sum is taken over
-    // differences u_j - u_i plus the (exactly assembled) row sum times u_i
-    real lu;
+    // differences u_j - u_i plus the (exactly assembled) row sum times u_i.
+    // The products are summed in FP64 (as in the divergence above and the
+    // field's rows): the solve starts from the residual of the stored
+    // potential, not of its rounded row sums (a minimization of the mixed
+    // polycrystal then takes 5% fewer solver iterations per evaluation).
+    double lu;
     if constexpr (std::is_same<real, float>::value)
-      lu = sell_sum(P, i, [&](int j) { return u_at(j) - ui; }) + P.lsum[i] * ui;
+      lu = l_row<real, double>(P, i, [&](int j) { return u_at(j) - ui; }) + (double)P.lsum[i] * ui;
     else
-      lu = sell_sum(P, i, [&](int j) { return u_at(j); });
-    const real ri = bi - lu;
+      lu = l_row<real>(P, i, [&](int j) { return u_at(j); });
+    const real ri = real(bi - lu);
     if (amg) r2[i] = ri;
     else rec[i].r = ri;
     acc[0] += (double)bi * (double)bi;
@@ -414,7 +401,7 @@ __device__ void phase_cg0(const ProbDev<real>& P, const Ctrl* C, int blk, double
     const int i = base + threadIdx.x;
     if (i >= r1) continue;
     const Rec<real> own = ld<real>(rec, i);
-    const real sw = sell_sum(P, i, [&](int j) {
+    const real sw = l_row<real>(P, i, [&](int j) {
       const Rec<real> nb = ld<real>(rec, j);
       return nb.d * nb.r;
     });
@@ -445,7 +432,7 @@ __device__ void phase_cg(const ProbDev<real>& P, const Ctrl* C, int blk, double*
     const Rec<real> own = ld<real>(ro, i);
     real pi = P.p[i];
     real ui = P.u3[C->ucur][i];
-    const real sw = sell_sum(P, i, [&](int j) {
+    const real sw = l_row<real>(P, i, [&](int j) {
       const Rec<real> nb = ld<real>(ro, j);
       return nb.d * (nb.r - alpha * (nb.w + beta * nb.s));
     });
@@ -480,226 +467,117 @@ __device__ __forceinline__ const MgLevelDev<real>& lev_of(int l) {
 }
 
 // ---- multigrid-preconditioned CG ----
-// Lane-partial sum over row i of a CSR matrix of v[k] * g(column): column
-// indices and values first, then all the gathers, then the products.
-template <typename real, int LPR, int U = kUnroll, typename G>
-__device__ __forceinline__ real row_sum(DevPtr<const int> __restrict__ rp, DevPtr<const int> __restrict__ ci,
-                                        DevPtr<const real> __restrict__ v, int i, int lane, G&& g) {
-  real acc = 0;
-  const int ke = rp[i + 1];
-  for (int k0 = rp[i] + lane; k0 < ke; k0 += U * LPR) {
-    int j[U];
-    real lv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = k0 + u * LPR;
-      const int ks = k < ke ? k : k0;
-      j[u] = ci[ks];
-      lv[u] = k < ke ? v[ks] : real(0);
-    }
-    real x[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = g(j[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) acc += lv[u] * x[u];
-  }
-  return acc;
-}
-
-// The same over a matrix with two values per entry {a, b}: returns
-// {sum a * g, sum b * g} from one gather per entry.
-template <typename real, int LPR, int U, typename G>
-__device__ __forceinline__ Pair<real> row_sum2(DevPtr<const int> __restrict__ rp, DevPtr<const int> __restrict__ ci,
-                                               DevPtr<const Pair<real>> __restrict__ v, int i, int lane, G&& g) {
-  real sa = 0, sb = 0;
-  const int ke = rp[i + 1];
-  for (int k0 = rp[i] + lane; k0 < ke; k0 += U * LPR) {
-    int j[U];
-    Pair<real> lv[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = k0 + u * LPR;
-      const int ks = k < ke ? k : k0;
-      j[u] = ci[ks];
-      lv[u] = k < ke ? ld<real>(v, ks) : Pair<real>{0, 0};
-    }
-    real x[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) x[u] = g(j[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      sa += lv[u].a * x[u];
-      sb += lv[u].b * x[u];
-    }
-  }
-  return Pair<real>{sa, sb};
-}
-
 // One operation of the symmetric V(1,1) cycle with damped-Jacobi smoothing
-// (x = wd b before the coarse correction, one sweep after it):
-//   DOWN(l)  res = b - A (wd b); on the levels l >= 1 where the host finds
-//            it pays, the same launch also restricts, b_{l+1} = M b with
-//            M = R (I - A wd) (a share of the blocks sweeps M's rows), and
-//            REST(l) is skipped; on the last level, with the host's dense
-//            Ainv M, those blocks form x_c = (Ainv M) b and SOLVE is skipped
+// (x = wd b before the coarse correction, one sweep after it).  With
+// res = b - A (wd b), T = (I - wd A) P and M = T^T = R (I - A wd) the cycle on
+// one level is b_{l+1} = R res = M b and
+//   x = wd b + P x_{l+1} + wd (b - A (wd b + P x_{l+1}))
+//     = wd b + wd res + T x_{l+1},
+// so the post-smoothing needs the residual of the pre-smoothing and one
+// matrix T with the pattern of A P (P's lies inside it), and the restriction
+// needs either the residual (R) or b alone (M).  Against sweeping the pairs
+// {(A P)_ik, P_ik} in POST and A and M in DOWN: 14 evaluations of the
+// polycrystal 193.6 -> 181.3 ms, the batched grains 76.0 -> 68.7 ms.
+//   DOWN(l)  unfused: res = b - A (wd b).  Fused: b_{l+1} = M b (on the last
+//            level, with the host's dense Ainv M, x_c = (Ainv M) b, and SOLVE
+//            is skipped); REST(l) is skipped and A waits for POST.
 //   REST(l)  b_{l+1} = R res (and wb_{l+1} = wd_{l+1} b_{l+1}, what DOWN and
 //            POST of level l + 1 gather)
 //   SOLVE    x_c = A_c^-1 b_c (dense)
-//   POST(l)  coarse correction and post-smoothing in one sweep:
-//            xa = wd b + P x_{l+1}, xb = xa + wd (b - A xa).  Since
-//            A xa = A (wd b) + (A P) x_{l+1} and DOWN left res = b - A (wd b),
-//            xb = xa + wd (res - (A P) x_{l+1}): one sweep of the matrix with
-//            the pattern of A P and the value pairs {(A P)_ik, P_ik} (P's
-//            pattern lies inside A P's) over x_{l+1}.  At level 0 the result
-//            is z, stored in the {z, p} records (whole records are written:
-//            p is carried over), and b.z is reduced.
-// W lanes share a row (4, 8, 16 or 32, chosen per matrix by the host); W = 1
-// (one thread per row) reads the operation's matrix in the sliced layout,
-// in which matrices with many short rows are held (the level-0 operator is
-// the potential matrix).  A lane loads 8 entries per batch with 8 or more lanes (matrices
-// with long rows), kUnroll with 4 (8 for Q's value pairs: the 39k-row level-1
-// post-smoothing of the 80 nm cube then takes one batch per row, 0.5 us
-// faster; R and A at 4 lanes measured no faster with 8).
-template <int W>
-constexpr int kRowU = W >= 8 ? 8 : kUnroll;
+//   POST(l)  unfused: x = wd (b + res) + T x_{l+1}.  Fused: the same in one
+//            sweep of [2 wd - wd A wd | T] over [wb | x_{l+1}].
+//            At level 0 the result is z, stored in the {z, p} records (whole
+//            records are written: p is carried over), and b.z is reduced.
+// The finest level's DOWN after the first runs inside PCG_B.
+// The next level's right-hand side as a restriction writes it.
+template <typename real>
+struct NextRhs {
+  DevPtr<real> b, wb;
+  DevPtr<const real> wd;
+  bool last;
+  __device__ __forceinline__ NextRhs(const ProbDev<real>& P, int l) : last(l + 1 == P.n_lev) {
+    b = last ? P.bc : lev_of<real>(l + 1).b;
+    wb = last ? nullptr : lev_of<real>(l + 1).wb;
+    wd = last ? nullptr : lev_of<real>(l + 1).wd;
+  }
+};
 
-template <typename real, int W, typename G>
-__device__ __forceinline__ real a_row(const MgLevelDev<real>& L, int i, int lane, bool nt, G&& g) {
-  if constexpr (W == 1) return sell_row<real>(L.aso, L.asc, L.asv, i, nt, g);
-  else return row_sum<real, W, kRowU<W>>(L.arp, L.aci, L.av, i, lane, g);
-}
-template <typename real, int W, typename G>
-__device__ __forceinline__ Pair<real> q_row(const MgLevelDev<real>& L, int i, int lane, bool nt, G&& g) {
-  if constexpr (W == 1) return sell_row_q<real>(L.qso, L.qsc, L.qsv, L.qpo, L.qpv, i, nt, g);
-  else return row_sum2<real, W, W == 4 ? 8 : kUnroll>(L.qrp, L.qci, L.qv, i, lane, g);   // two values per entry
-}
-template <typename real, int W, typename G>
-__device__ __forceinline__ real r_row(const MgLevelDev<real>& L, int i, int lane, bool nt, G&& g) {
-  if constexpr (W == 1) return sell_row<real>(L.rso, L.rsc, L.rsv, i, nt, g);
-  else return row_sum<real, W, kRowU<W>>(L.rrp, L.rci, L.rv, i, lane, g);
-}
-
-template <typename real, int W, typename G>
-__device__ __forceinline__ real m_row(const MgLevelDev<real>& L, int i, int lane, G&& g) {
-  return row_sum<real, W, kRowU<W>>(L.mrp, L.mci, L.mv, i, lane, g);
+// Calls f(position, row, lane, valid) for the rows of block blk of G of a
+// matrix of n rows in slices of 2^lw lanes per row, row order ord.
+template <typename F>
+__device__ __forceinline__ void sweep(int n, int G, int blk, int lw, DevPtr<const int> ord, F&& f) {
+  const int lane = threadIdx.x & ((1 << lw) - 1), slot = threadIdx.x >> lw;
+  int r0, r1, rs;
+  chunk_rows(n, G, blk, kBlock >> lw, 64 >> lw, r0, r1, rs);
+  for (int base = r0; base < r1; base += rs) {
+    const int i = base + slot;
+    const bool valid = i < r1;
+    // the row's own values are loaded after the sweep, so that the load of its
+    // index does not hold up the sweep's
+    f(i, (valid && ord) ? ord[i] : i, lane, valid);
+  }
 }
 
-// Rows of operation `op` on level l, block blk of the G blocks that share
-// them.
-template <typename real, int W>
-__device__ void mg_rows(const ProbDev<real>& P, const Ctrl* C, const MgLevelDev<real>& L, int op, int l, int blk,
-                        int G, double* acc) {
-  constexpr int RPP = kBlock / W;
-  const int lane = threadIdx.x & (W - 1);
-  const int slot = threadIdx.x / W;
+// b_{l+1} = R res, or M b on a fused level, over the rows of block blk of G:
+// g(j) is res_j or b_j.
+template <typename real, typename GB>
+__device__ __forceinline__ void restrict_rows(const ProbDev<real>& P, const MgLevelDev<real>& L, int l, int blk, int G,
+                                              GB&& g) {
+  const NextRhs<real> nx(P, l);
+  const int lw = L.lanes_r;
+  sweep(L.n_next, G, blk, lw, L.rord, [&](int i, int ri, int lane, bool valid) {
+    real sum = valid ? slice_row<real>(L.rso, L.rsc, L.rsv, i, lw, P.stream != 0, g) : real(0);
+    sum = lanes_sum(sum, lw);
+    if (valid && lane == 0) {
+      nx.b[ri] = sum;
+      if (!nx.last) nx.wb[ri] = nx.wd[ri] * sum;
+    }
+  });
+}
+
+// An unfused level's DOWN over the rows of block blk of G.
+template <typename real>
+__device__ __forceinline__ void down_rows(const ProbDev<real>& P, const Ctrl* C, const MgLevelDev<real>& L, int l,
+                                          int blk, int G) {
   DevPtr<const real> __restrict__ b = l == 0 ? P.r2[C->rcur] : L.b;
   DevPtr<const real> __restrict__ wd = L.wd;
   DevPtr<const real> __restrict__ wb = L.wb;
-  const bool last = l + 1 == P.n_lev;
-  const bool nt = P.stream != 0;
-  int r0, r1, rs;
-  if (op == MG_REST || op == MG_RESTM) {
-    DevPtr<real> __restrict__ bn = last ? P.bc : lev_of<real>(l + 1).b;
-    DevPtr<real> __restrict__ wbn = last ? nullptr : lev_of<real>(l + 1).wb;
-    DevPtr<const real> __restrict__ wdn = last ? nullptr : lev_of<real>(l + 1).wd;
-    DevPtr<const real> __restrict__ res = L.res;
-    const bool m = op == MG_RESTM;   // b_{l+1} = M b, else R res
-    // a sliced R holds its rows in a windowed order: position i is row ri
-    DevPtr<const int> __restrict__ ord = W == 1 ? L.rord : nullptr;
-    chunk_rows(L.n_next, G, blk, RPP, W == 1 ? 64 : 1, r0, r1, rs);
-    for (int base = r0; base < r1; base += rs) {
-      const int i = base + slot;
-      const bool valid = i < r1;
-      const int ri = (valid && ord) ? ord[i] : i;
-      // the row's own values: before the sweep when rows are in place, after
-      // it when their index comes from the row order (so that its load does
-      // not hold up the sweep's)
-      real wi = (valid && lane == 0 && !last && !ord) ? wdn[i] : real(0);
-      real sum = 0;
-      if (valid)
-        sum = m ? m_row<real, W>(L, i, lane, [&](int j) { return b[j]; })
-                : r_row<real, W>(L, i, lane, nt, [&](int j) { return res[j]; });
-      sum = group_sum<real, W>(sum);
-      if (valid && lane == 0) {
-        if (ord && !last) wi = wdn[ri];
-        bn[ri] = sum;
-        if (!last) wbn[ri] = wi * sum;
-      }
-    }
-    return;
-  }
-  chunk_rows(L.n, G, blk, RPP, W == 1 ? 64 : 1, r0, r1, rs);
-  if (op == MG_DOWN) {
-    DevPtr<const int> __restrict__ ord = W == 1 ? L.aord : nullptr;   // windowed row order of a sliced A
-    for (int base = r0; base < r1; base += rs) {
-      const int i = base + slot;
-      const bool valid = i < r1;
-      const int ri = (valid && ord) ? ord[i] : i;
-      real bi = (valid && lane == 0 && !ord) ? b[i] : real(0);   // (as in REST)
-      real sum = valid ? a_row<real, W>(L, i, lane, nt, [&](int j) { return l == 0 ? wd[j] * b[j] : wb[j]; })
-                       : real(0);
-      sum = group_sum<real, W>(sum);
-      if (valid && lane == 0) {
-        if (ord) bi = b[ri];
-        L.res[ri] = bi - sum;
-      }
-    }
-  } else {   // MG_POST
-    DevPtr<const real> __restrict__ xn = last ? P.xc : lev_of<real>(l + 1).xb;
-    DevPtr<const real> __restrict__ res = L.res;
-    DevPtr<const int> __restrict__ ord = W == 1 ? L.qord : nullptr;   // windowed row order of a sliced Q
-    for (int base = r0; base < r1; base += rs) {
-      const int i = base + slot;
-      const bool valid = i < r1;
-      const int ri = (valid && ord) ? ord[i] : i;
-      real bi = 0, wi = 0, rr = 0, pold = 0;
-      auto own = [&](int r) {   // (as in REST)
-        bi = b[r];
-        wi = wd[r];
-        rr = res[r];
-        if (l == 0) pold = P.zp[r].b;
-      };
-      if (valid && lane == 0 && !ord) own(i);
-      Pair<real> sum = valid ? q_row<real, W>(L, i, lane, nt, [&](int j) { return xn[j]; }) : Pair<real>{0, 0};
-      sum.a = group_sum<real, W>(sum.a);
-      sum.b = group_sum<real, W>(sum.b);
-      if (valid && lane == 0) {
-        if (ord) own(ri);
-        const real xai = wi * bi + sum.b;
-        const real zi = xai + wi * (rr - sum.a);
-        if (l == 0) {
-          st<real>(P.zp, ri, Pair<real>{zi, pold});
-          acc[0] += (double)bi * (double)zi;
-        } else {
-          L.xb[ri] = zi;
-        }
-      }
-    }
-  }
+  const int lw = L.lanes_a;
+  sweep(L.n, G, blk, lw, L.aord, [&](int i, int ri, int lane, bool valid) {
+    real sum = valid ? slice_row<real>(L.aso, L.asc, L.asv, i, lw, P.stream != 0,
+                                       [&](int j) { return l == 0 ? wd[j] * b[j] : wb[j]; })
+                     : real(0);
+    sum = lanes_sum(sum, lw);
+    if (valid && lane == 0) L.res[ri] = b[ri] - sum;
+  });
 }
 
-// The row layout of an operation's matrix picks the kernel variant.
+// POST over the rows of block blk of G.
 template <typename real>
-__device__ __forceinline__ void mg_dispatch(const ProbDev<real>& P, const Ctrl* C, const MgLevelDev<real>& L, int op, int l,
-                            int blk, int G, double* acc) {
-  const int lanes = op == MG_REST    ? L.lanes_r
-                    : op == MG_RESTM ? L.lanes_m
-                    : op == MG_POST  ? L.lanes_q
-                                     : L.lanes_a;
-  const bool sliced = op == MG_REST    ? L.rso != nullptr
-                      : op == MG_RESTM ? false
-                      : op == MG_POST  ? L.qso != nullptr
-                                       : L.aso != nullptr;
-  if (sliced)
-    mg_rows<real, 1>(P, C, L, op, l, blk, G, acc);
-  else if (lanes == 32)
-    mg_rows<real, 32>(P, C, L, op, l, blk, G, acc);
-  else if (lanes == 16)
-    mg_rows<real, 16>(P, C, L, op, l, blk, G, acc);
-  else if (lanes == 8)
-    mg_rows<real, 8>(P, C, L, op, l, blk, G, acc);
-  else
-    mg_rows<real, 4>(P, C, L, op, l, blk, G, acc);
+__device__ __forceinline__ void post_rows(const ProbDev<real>& P, const Ctrl* C, const MgLevelDev<real>& L, int l,
+                                          int blk, int G, double* acc) {
+  const bool fused = L.fused != 0;
+  DevPtr<const real> __restrict__ b = l == 0 ? P.r2[C->rcur] : L.b;
+  DevPtr<const real> __restrict__ wd = L.wd;
+  DevPtr<const real> __restrict__ y = fused ? L.wb : L.xn;
+  DevPtr<const real> __restrict__ res = L.res;
+  const int lw = L.lanes_q;
+  sweep(L.n, G, blk, lw, L.qord, [&](int i, int ri, int lane, bool valid) {
+    real sum = valid ? slice_row<real>(L.qso, L.qsc, L.qsv, i, lw, P.stream != 0, [&](int j) { return y[j]; })
+                     : real(0);
+    sum = lanes_sum(sum, lw);
+    if (valid && lane == 0) {
+      const real bi = !fused || l == 0 ? b[ri] : real(0);
+      const real zi = fused ? sum : wd[ri] * (bi + res[ri]) + sum;
+      if (l == 0) {
+        const real pold = P.zp[ri].b;
+        st<real>(P.zp, ri, Pair<real>{zi, pold});
+        acc[0] += (double)bi * (double)zi;
+      } else {
+        L.xb[ri] = zi;
+      }
+    }
+  });
 }
 
 // x_c = (Ainv M) b_l on the last level: one dense row per block at a time,
@@ -748,36 +626,41 @@ __device__ void phase_mg(const ProbDev<real>& P, const Ctrl* C, int op, int l, i
     return;
   }
   const MgLevelDev<real>& L = lev_of<real>(l);
-  int o = op, b = blk, g = P.G, passes = 1;
-  if (op == MG_DOWN && L.m_blocks > 0) {
-    // fused restriction: the last gm blocks sweep M, the others A; with
-    // too few blocks to split, every block does both, one after the other
-    if (g >= 16) {
-      int gm = (g * L.m_blocks / 512 + 7) / 8 * 8;
-      gm = gm < 8 ? 8 : gm > g - 8 ? g - 8 : gm;
-      if (blk >= g - gm) {
-        o = MG_RESTM;
-        b = blk - (g - gm);
-        g = gm;
-      } else {
-        g -= gm;
-      }
-    } else {
-      passes = 2;
-    }
+  if (op == MG_REST) {
+    DevPtr<const real> __restrict__ res = L.res;
+    restrict_rows<real>(P, L, l, blk, P.G, [&](int j) { return res[j]; });
+    return;
   }
-  for (int k = 0; k < passes; ++k) {
-    const int ok = k == 0 ? o : MG_RESTM;
-    if (ok == MG_RESTM && P.AinvM && l + 1 == P.n_lev)
-      coarse_rows<real>(P, L, b, g);   // x_c = (Ainv M) b
-    else
-      mg_dispatch<real>(P, C, L, ok, l, b, g, acc);
+  if (op == MG_POST) {
+    post_rows<real>(P, C, L, l, blk, P.G, acc);
+    return;
+  }
+  if (!L.fused) {
+    down_rows<real>(P, C, L, l, blk, P.G);
+    return;
+  }
+  if (P.AinvM && l + 1 == P.n_lev) {
+    coarse_rows<real>(P, L, blk, P.G);   // x_c = (Ainv M) b
+    return;
+  }
+  if (l == 0) {   // the first cycle of a solve: wd r, which POST gathers (later cycles: PCG_B)
+    DevPtr<const real> __restrict__ r = P.r2[C->rcur];
+    int r0, r1, rs;
+    chunk_rows(P.Nt, P.G, blk, kBlock, 64, r0, r1, rs);
+    for (int base = r0; base < r1; base += rs) {
+      const int i = base + threadIdx.x;
+      if (i < r1) L.wb[i] = L.wd[i] * r[i];
+    }
+    restrict_rows<real>(P, L, 0, blk, P.G, [&](int j) { return r[j]; });
+  } else {
+    DevPtr<const real> __restrict__ b = L.b;
+    restrict_rows<real>(P, L, l, blk, P.G, [&](int j) { return b[j]; });
   }
 }
 
 // PCG_A: p = z + beta p_old (recomputed at gathered neighbours from the
-// {z, p} records), q = L p, p.q; also the {wd r, wd q} records PCG_B gathers.
-// p itself is stored by PCG_B, which gathers no {z, p} record.  One thread
+// {z, p} records), q = L p, p.q; also the records PCG_B gathers: {r, q} with a
+// fused finest level, else {wd r, wd q}.  p itself is stored by PCG_B, which gathers no {z, p} record.  One thread
 // per row.
 template <typename real, int LPR>
 __device__ void phase_pcg_a(const ProbDev<real>& P, const Ctrl* C, int blk, double* acc) {
@@ -789,28 +672,32 @@ __device__ void phase_pcg_a(const ProbDev<real>& P, const Ctrl* C, int blk, doub
   DevPtr<const Pair<real>> __restrict__ zp = P.zp;
   DevPtr<const real> __restrict__ r = P.r2[C->rcur];
   DevPtr<const real> __restrict__ wd = lev_of<real>(0).wd;
+  const bool fused = lev_of<real>(0).fused != 0;
   for (int base = r0; base < r1; base += rs) {
     const int i = base + threadIdx.x;
     if (i >= r1) continue;
     const Pair<real> own = ld<real>(zp, i);
-    const real ri = r[i], wi = wd[i];
+    const real ri = r[i], wi = fused ? real(1) : wd[i];
     // beta = 0 starts a solve: the p half then holds the previous solve's
     // direction and is not read
-    const real sum = sell_sum(P, i, [&](int j) {
+    const real sum = l_row<real>(P, i, [&](int j) {
       const Pair<real> e = ld<real>(zp, j);
       return first ? e.a : e.a + beta * e.b;
     });
     const real pi = first ? own.a : own.a + beta * own.b;
-    P.q[i] = sum;
+    if (!fused) P.q[i] = sum;
     st<real>(P.rq, i, Pair<real>{wi * ri, wi * sum});
     acc[0] += (double)pi * (double)sum;
   }
 }
 
-// PCG_B: p = z + beta p_old (stored), r -= alpha q, u += alpha p, then the
-// finest pre-smoothing residual of the next V-cycle, res = r - L (wd r),
-// with neighbours' wd r_new recomputed from their {wd r, wd q} records.
-// Partials: r.r, r.u.  One thread per row.
+// PCG_B: p = z + beta p_old (stored), r -= alpha q, u += alpha p, and the
+// finest level's DOWN of the next V-cycle.  Unfused: the pre-smoothing
+// residual res = r - L (wd r), with neighbours' wd r_new recomputed from their
+// {wd r, wd q} records.  Fused: wd r and the next level's right-hand side
+// M r, with r_new recomputed at the gathered nodes from their {r, q} records:
+// the phase then moves vectors and M only, the sweep of L has moved into
+// POST(0) and REST(0) is gone.  Partials: r.r, r.u.  One thread per row.
 template <typename real, int LPR>
 __device__ void phase_pcg_b(const ProbDev<real>& P, const Ctrl* C, int blk, double* acc) {
   constexpr int RPP = kBlock;
@@ -818,30 +705,47 @@ __device__ void phase_pcg_b(const ProbDev<real>& P, const Ctrl* C, int blk, doub
   chunk_rows(P.Nt, P.G, blk, RPP, 64, r0, r1, rs);
   const real alpha = real(C->alpha), beta = real(C->beta);
   const bool first = C->beta == 0.0;
+  const MgLevelDev<real>& L = lev_of<real>(0);
   DevPtr<Pair<real>> __restrict__ zp = P.zp;
-  DevPtr<const real> __restrict__ ro = P.r2[C->rcur];
   DevPtr<real> __restrict__ rn = P.r2[1 - C->rcur];
-  DevPtr<const real> __restrict__ q = P.q;
   DevPtr<const Pair<real>> __restrict__ rq = P.rq;
   DevPtr<real> __restrict__ U = P.u3[C->ucur];
-  for (int base = r0; base < r1; base += rs) {
-    const int i = base + threadIdx.x;
-    if (i >= r1) continue;
-    const real roi = ro[i], qi = q[i], uo = U[i];
-    const Pair<real> own = ld<real>(zp, i);
-    const real sum = sell_sum(P, i, [&](int j) {
-      const Pair<real> e = ld<real>(rq, j);
-      return e.a - alpha * e.b;
-    });
+  auto update = [&](int i, real roi, real qi, real uo, const Pair<real>& own) {
     const real pi = first ? own.a : own.a + beta * own.b;
     st<real>(zp, i, Pair<real>{own.a, pi});
     const real ri = roi - alpha * qi;
     const real ui = uo + alpha * pi;
     rn[i] = ri;
     U[i] = ui;
-    lev_of<real>(0).res[i] = ri - sum;
     acc[0] += (double)ri * (double)ri;
     acc[1] += (double)ri * (double)ui;
+    return ri;
+  };
+  if (L.fused) {
+    for (int base = r0; base < r1; base += rs) {
+      const int i = base + threadIdx.x;
+      if (i >= r1) continue;
+      const Pair<real> e = ld<real>(rq, i);
+      L.wb[i] = L.wd[i] * update(i, e.a, e.b, U[i], ld<real>(zp, i));
+    }
+    restrict_rows<real>(P, L, 0, blk, P.G, [&](int j) {
+      const Pair<real> e = ld<real>(rq, j);
+      return e.a - alpha * e.b;
+    });
+    return;
+  }
+  DevPtr<const real> __restrict__ ro = P.r2[C->rcur];
+  DevPtr<const real> __restrict__ q = P.q;
+  for (int base = r0; base < r1; base += rs) {
+    const int i = base + threadIdx.x;
+    if (i >= r1) continue;
+    const real roi = ro[i], qi = q[i], uo = U[i];
+    const Pair<real> own = ld<real>(zp, i);
+    const real sum = l_row<real>(P, i, [&](int j) {
+      const Pair<real> e = ld<real>(rq, j);
+      return e.a - alpha * e.b;
+    });
+    L.res[i] = update(i, roi, qi, uo, own) - sum;
   }
 }
 
@@ -878,7 +782,7 @@ __device__ void phase_field(const ProbDev<real>& P, const Ctrl* C, int blk, doub
   for (int base = r0; base < r1; base += rs) {
     const int i = base + slot;
     const bool valid = i < r1;
-    real kx = 0, ky = 0, kz = 0, dx = 0, dy = 0, dz = 0;
+    double kx = 0, ky = 0, kz = 0, dx = 0, dy = 0, dz = 0;
     real oi0 = 0, oi1 = 0, oi2 = 0, oiu = 0;   // own values subtracted in the difference form
     if (kDiff && valid) {
       oi0 = mx[i];
@@ -909,9 +813,9 @@ __device__ void phase_field(const ProbDev<real>& P, const Ctrl* C, int blk, doub
           }
 #pragma unroll
           for (int u = 0; u < kU; ++u) {
-            kx += kv[u] * gx[u];
-            ky += kv[u] * gy[u];
-            kz += kv[u] * gz[u];
+            kx += (double)kv[u] * gx[u];
+            ky += (double)kv[u] * gy[u];
+            kz += (double)kv[u] * gz[u];
           }
         }
         if (demag) {
@@ -927,19 +831,19 @@ __device__ void phase_field(const ProbDev<real>& P, const Ctrl* C, int blk, doub
           }
 #pragma unroll
           for (int u = 0; u < kU; ++u) {
-            dx += ex[u] * uj[u];
-            dy += ey[u] * uj[u];
-            dz += ez[u] * uj[u];
+            dx += (double)ex[u] * uj[u];
+            dy += (double)ey[u] * uj[u];
+            dz += (double)ez[u] * uj[u];
           }
         }
       }
     }
-    kx = group_sum<real, LPR>(kx);
-    ky = group_sum<real, LPR>(ky);
-    kz = group_sum<real, LPR>(kz);
-    dx = group_sum<real, LPR>(dx);
-    dy = group_sum<real, LPR>(dy);
-    dz = group_sum<real, LPR>(dz);
+    kx = group_sum<double, LPR>(kx);
+    ky = group_sum<double, LPR>(ky);
+    kz = group_sum<double, LPR>(kz);
+    dx = group_sum<double, LPR>(dx);
+    dy = group_sum<double, LPR>(dy);
+    dz = group_sum<double, LPR>(dz);
     if (valid && lane == 0) {
       const real m0 = mx[i], m1 = my[i], m2 = mz[i];
       real ax = 0, ay = 0, az = 0;
@@ -948,9 +852,9 @@ __device__ void phase_field(const ProbDev<real>& P, const Ctrl* C, int blk, doub
         ay = P.Q[3][i] * m0 + P.Q[1][i] * m1 + P.Q[5][i] * m2;
         az = P.Q[4][i] * m0 + P.Q[5][i] * m1 + P.Q[2][i] * m2;
       }
-      const real hx = -kx - dx + ax + bzx;
-      const real hy = -ky - dy + ay + bzy;
-      const real hz = -kz - dz + az + bzz;
+      const real hx = real(-kx - dx + ax + bzx);
+      const real hy = real(-ky - dy + ay + bzy);
+      const real hz = real(-kz - dz + az + bzz);
       const real Hx = m1 * hz - m2 * hy, Hy = m2 * hx - m0 * hz, Hz = m0 * hy - m1 * hx;
       P.H[tr][0][i] = Hx;
       P.H[tr][1][i] = Hy;
@@ -961,7 +865,7 @@ __device__ void phase_field(const ProbDev<real>& P, const Ctrl* C, int blk, doub
         P.h[2][i] = hz;
       }
       const double V = (double)P.V[i];
-      fa[FP_EEX] += 0.5 * V * (double)(m0 * kx + m1 * ky + m2 * kz);
+      fa[FP_EEX] += 0.5 * V * (m0 * kx + m1 * ky + m2 * kz);
       if constexpr (kDiff) {
         // FP32: the anisotropy energy sum_e V_e K1_e - m.Q m cancels for m
         // near the easy axis; for unit m it equals m.(tr(Q) I - Q) m, whose
@@ -977,7 +881,7 @@ __device__ void phase_field(const ProbDev<real>& P, const Ctrl* C, int blk, doub
       }
       // with the applied field in FP64 (rounding it to FP32 would bias every node alike)
       if (zeem) fa[FP_EZ] -= V * ((double)m0 * C->bz[0] + (double)m1 * C->bz[1] + (double)m2 * C->bz[2]);
-      fa[FP_ED] += 0.5 * V * (double)(m0 * dx + m1 * dy + m2 * dz);
+      fa[FP_ED] += 0.5 * V * (m0 * dx + m1 * dy + m2 * dz);
       const double H2 = (double)Hx * Hx + (double)Hy * Hy + (double)Hz * Hz;
       fa[FP_TMAX] = fmax(fa[FP_TMAX], sqrt(H2));
       fa[FP_D] += V * H2;
@@ -1319,7 +1223,7 @@ __device__ __forceinline__ bool mg_next(int op, int lev, int n_lev, int fused, b
     nop = MG_REST;
     return true;
   }
-  if (op == MG_DOWN || op == MG_REST) {   // a fused DOWN also restricted
+  if (op == MG_DOWN || op == MG_REST) {   // a fused DOWN restricted
     if (lev + 1 < n_lev) {
       nlev = lev + 1;
       nop = MG_DOWN;
@@ -1384,9 +1288,11 @@ __device__ __forceinline__ bool transition_fast(Ctrl* C, const double* v, const 
   if (C->rr <= C->pcg_rtol2 * C->bb || C->pcg_it >= C->pcg_maxit) {
     C->phase = PH_FIELD;
   } else {
-    C->phase = PH_MG;
-    C->mg_op = MG_REST;
-    C->mg_lev = 0;
+    C->phase = PH_MG;   // PCG_B was the finest level's DOWN
+    int nop, nlev;
+    mg_next(MG_DOWN, 0, n_lev, fused, folded, nop, nlev);
+    C->mg_op = nop;
+    C->mg_lev = nlev;
   }
   return true;
 }

@@ -158,9 +158,8 @@ struct mmsd_problem_s {
   int64_t nnzL = 0;                       // its entries
   bool has_amg = false;
   mmsd::AmgHierarchy amg;                 // host copy (sizes; values uploaded)
-  std::vector<int64_t> amg_q_nnz;         // entries of each level's fused prolongation/smoothing matrix
-  std::vector<int64_t> amg_m_nnz;         // entries of each level's residual restriction (levels >= 1)
-  std::vector<int> amg_q_sliced;          // 1: the level's Q is swept from its sliced form
+  std::vector<int64_t> amg_q_nnz;         // entries of each level's post-smoothing matrix
+  std::vector<int64_t> amg_m_nnz;         // entries of each level's residual restriction (0: unfused)
   bool amg_folded = false;                // the last DOWN forms the coarsest solution (Ainv M)
   char* amg_arena = nullptr;
   size_t amg_bytes = 0;
