@@ -512,6 +512,10 @@ int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
     return MMSD_E_NOMEM;
   }
   p->arena_bytes = L.total;
+  MMSD_HIP(hipHostMalloc((void**)&p->mirror, sizeof(Mirror) + 2 * sizeof(Ctrl),
+                         hipHostMallocMapped | hipHostMallocCoherent));
+  std::memset(p->mirror, 0, sizeof(Mirror) + 2 * sizeof(Ctrl));
+  p->hpoll = reinterpret_cast<Ctrl*>(p->mirror + 1);
   hipStream_t st = c->stream;
   char* base = p->arena;
   MMSD_HIP(hipMemsetAsync(base, 0, L.total, st));
@@ -606,6 +610,7 @@ int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
   P.p = (real*)(base + L.p);
   for (int k = 0; k < 2; ++k) P.rec[k] = (Rec<real>*)(base + L.rec[k]);
   P.ndone = nullptr;
+  P.mirror = p->mirror;
   P.part = (double*)(base + L.part);
   P.ctrl = (Ctrl*)(base + L.ctrl);
   p->dctrl = P.ctrl;
@@ -628,6 +633,7 @@ int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
 int set_launch(mmsd_problem p, int lpr, int max_blocks) {
   const int G = blocks_for(std::max<int64_t>(p->A.N, p->A.Nt), lpr, max_blocks);
   if (G == p->G && lpr == p->lpr) return MMSD_OK;
+  MMSD_HIP(hipStreamSynchronize(p->ctx->stream));   // the last run's launches may still be in flight
   for (auto& kv : p->graphs) (void)hipGraphExecDestroy(kv.second);
   p->graphs.clear();
   p->lpr = lpr;
@@ -703,7 +709,7 @@ int arm(mmsd_problem p, const Resolved& r, int stage, int store_h) {
                          mixed ? std::ldexp(1.0, -20) : 0.0};
   MMSD_HIP(launch_ctrl_init(p->dctrl, kArmSlot, stage, r.terms, r.M, r.rule, r.maxit, store_h,
                             (r.terms & MMSD_DEMAG) ? 1 : 0, p->acc, r.precond, mixed ? 1 : 0,
-                            mixed ? kMixedHalvings : 0, r.stop, p->ucur, (long long)r.max_evals, dp,
+                            mixed ? kMixedHalvings : 0, r.stop, p->ucur, ++p->run, (long long)r.max_evals, dp,
                             p->ctx->stream));
   return MMSD_OK;
 }
@@ -825,119 +831,165 @@ bool run_timed_out(std::chrono::steady_clock::time_point t0) {
   return std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count() > limit;
 }
 
-int ensure_pinned(mmsd_problem p) {
-  if (!p->hctrl) MMSD_HIP(hipHostMalloc((void**)&p->hctrl, 4 * sizeof(Ctrl), hipHostMallocDefault));
-  return MMSD_OK;
-}
-
 namespace {
 
-// Arm, then launch batches until the control block reports DONE.
+// The run's outcome in the problem's mirror, or null while it runs.
+const Ctrl* outcome(mmsd_problem p) {
+  return __atomic_load_n(&p->mirror->run, __ATOMIC_ACQUIRE) == p->run ? &p->mirror->ctrl : nullptr;
+}
+
+// Launches of the next batch after `launched`.  Two batches are kept in
+// flight, so on average one and a half batches of launches find the problem
+// done (about 2 us each), while every batch costs a gap of about 7 us on the
+// stream: the batches grow as the square root of the launches so far.  A
+// small first one serves an evaluation without the stray field, which needs
+// three launches.  With batches that doubled to 64 at once and a copy of the
+// control state behind each, an evaluation of the 20 nm cube issued 248
+// launches for 118; it took 1.05 and takes 0.91 ms, one without the stray
+// field 199 and 144 us.
+int next_batch(int64_t launched) {
+  return launched == 0 ? 8 : launched < 256 ? 16 : launched < 1024 ? 32 : 64;
+}
+// Batches between two looks at the phase counter (the stall guard).
+constexpr int kGuardBatches = 32;
+
+// Arm, then launch batches until the problem's mirror holds the outcome.  The
+// launches still in flight then find a finished problem and do nothing; what
+// follows on the stream waits for them.
 int run_single(mmsd_problem p, const Resolved& r, int stage, int store_h, mmsd_result* out) {
   mmsd_ctx c = p->ctx;
   std::lock_guard<std::mutex> lk(c->mu);
   auto t0 = std::chrono::steady_clock::now();
   MMSD_HIP(hipSetDevice(c->device));
   int rc;
-  if ((rc = ensure_pinned(p)) || (rc = arm(p, r, stage, store_h))) return rc;
+  if ((rc = arm(p, r, stage, store_h))) return rc;
   hipStream_t st = c->stream;
   std::vector<Table> tabs{{p->precision, p->dprob, p->dblk, 1, p->G, p->lpr}};
-  int B = 8, cur = 0, stalls = 0;
+  for (hipEvent_t& e : c->batch_ev)
+    if (!e) MMSD_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  int64_t issued = 0, finished = 0, launched = 0;   // batches and launches
+  int stalls = 0;
   long long last_done = -1;
-  bool have_prev = false;
-  int64_t launched = 0;
-  hipEvent_t ev[2];
-  MMSD_HIP(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming));
-  MMSD_HIP(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming));
-  for (;;) {
-    if ((rc = issue(c, tabs, B, &p->graphs))) break;
-    launched += B;
-    if (hipMemcpyAsync(&p->hctrl[2 * cur], p->dctrl, 2 * sizeof(Ctrl), hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipEventRecord(ev[cur], st) != hipSuccess) {
-      rc = hip_fail(hipGetLastError(), "poll copy");
-      break;
-    }
-    if (have_prev) {
-      hipError_t e = hipEventSynchronize(ev[1 - cur]);
-      if (e != hipSuccess) {
-        rc = hip_fail(e, "poll wait");
+  const Ctrl* C = nullptr;
+  while (!rc && !(C = outcome(p))) {
+    if (issued - finished < 2) {
+      const int B = next_batch(launched);
+      if ((rc = issue(c, tabs, B, &p->graphs))) break;
+      launched += B;
+      const bool guard = issued % kGuardBatches == kGuardBatches - 1;
+      if ((guard && hipMemcpyAsync(p->hpoll, p->dctrl, 2 * sizeof(Ctrl), hipMemcpyDeviceToHost, st) != hipSuccess) ||
+          hipEventRecord(c->batch_ev[issued & 1], st) != hipSuccess) {
+        rc = hip_fail(hipGetLastError(), "batch event");
         break;
       }
-      const Ctrl& H = latest(&p->hctrl[2 * (1 - cur)]);
-      if (H.phase == PH_DONE) break;
-      // every launch of an unfinished problem executes one phase; a counter
-      // that stops moving means the phase machine is stuck
-      if (H.launches_done == last_done) {
-        if (++stalls >= 3) {
-          set_error("device phase machine stalled");
-          rc = MMSD_E_HIP;
-          break;
-        }
-      } else {
-        stalls = 0;
-        last_done = H.launches_done;
-      }
-      if (run_timed_out(t0)) {
-        set_error("run exceeded MMSD_RUN_TIMEOUT_S");
+      ++issued;
+      continue;
+    }
+    const hipError_t e = hipEventQuery(c->batch_ev[finished & 1]);
+    if (e == hipErrorNotReady) {
+      for (int k = 0; k < 16; ++k) __builtin_ia32_pause();
+      continue;
+    }
+    if (e != hipSuccess) {
+      rc = hip_fail(e, "batch wait");
+      break;
+    }
+    // every launch of an unfinished problem executes one phase; a counter
+    // that stops moving means the phase machine is stuck
+    if (finished % kGuardBatches == kGuardBatches - 1) {
+      const long long done = latest(p->hpoll).launches_done;
+      stalls = done == last_done && latest(p->hpoll).phase != PH_DONE ? stalls + 1 : 0;
+      last_done = done;
+      if (stalls >= 3) {
+        set_error("device phase machine stalled");
         rc = MMSD_E_HIP;
         break;
       }
     }
-    have_prev = true;
-    cur ^= 1;
-    B = std::min(B * 2, 64);
+    ++finished;
+    if (run_timed_out(t0)) {
+      set_error("run exceeded MMSD_RUN_TIMEOUT_S");
+      rc = MMSD_E_HIP;
+      break;
+    }
   }
-  hipError_t e = hipStreamSynchronize(st);
-  (void)hipEventDestroy(ev[0]);
-  (void)hipEventDestroy(ev[1]);
-  if (rc) return rc;
-  if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  const Ctrl& C = latest(&p->hctrl[2 * cur]);
+  if (rc) {
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(st);
+    return rc;
+  }
   if (c->timing.stride > 0) {
+    MMSD_HIP(hipStreamSynchronize(st));
     if ((rc = drain_timing(c))) return rc;
-    c->timing.bytes += run_bytes(p, C);
+    c->timing.bytes += run_bytes(p, *C);
   }
-  p->acc = C.acc;
-  p->ucur = C.ucur;
-  p->h_valid = store_h != 0 && C.status == MMSD_OK;
-  p->last_launches = launched;
+  p->acc = C->acc;
+  p->ucur = C->ucur;
+  p->h_valid = store_h != 0 && C->status == MMSD_OK;
   double secs = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-  fill_result(p, C, out, secs, C.launches_done);
-  return C.status;
+  fill_result(p, *C, out, secs, C->launches_done);
+  return C->status;
+}
+
+// The three components of m or h lie one behind the other in the arena, each
+// aligned: they are copied in one piece.
+template <typename real>
+size_t component_pitch(mmsd_problem p) {
+  return align_up(sizeof(real) * (size_t)p->A.N) / sizeof(real);
+}
+
+// Runs f(a, b) over the nodes, on several threads when there are enough for
+// their start to pay.
+void over_nodes(int64_t n, const std::function<void(int64_t, int64_t)>& f) {
+  if (n < 262144) f(0, n);
+  else parallel_for(n, f);
+}
+
+// Three components from the device into an AoS host array.
+template <typename real>
+int components_to_host(mmsd_problem p, real* const comp[3], double* out) {
+  const size_t N = p->A.N, pitch = component_pitch<real>(p);
+  std::vector<real> tmp(3 * pitch);
+  hipStream_t st = p->ctx->stream;
+  MMSD_HIP(hipMemcpyAsync(tmp.data(), comp[0], sizeof(real) * (2 * pitch + N), hipMemcpyDeviceToHost, st));
+  MMSD_HIP(hipStreamSynchronize(st));
+  over_nodes(N, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i)
+      for (int k = 0; k < 3; ++k) out[3 * i + k] = (double)tmp[k * pitch + i];
+  });
+  return MMSD_OK;
 }
 
 template <typename real>
 int copy_m_to_host(mmsd_problem p, double* m_out) {
-  const Prob<real>& P = desc_of<real>(p);
-  const int N = p->A.N;
-  std::vector<real> tmp(3 * (size_t)N);
-  hipStream_t st = p->ctx->stream;
-  for (int k = 0; k < 3; ++k)
-    MMSD_HIP(hipMemcpyAsync(tmp.data() + (size_t)k * N, P.m[p->acc][k], sizeof(real) * N, hipMemcpyDeviceToHost, st));
-  MMSD_HIP(hipStreamSynchronize(st));
-  for (int i = 0; i < N; ++i)
-    for (int k = 0; k < 3; ++k) m_out[3 * (size_t)i + k] = (double)tmp[(size_t)k * N + i];
-  return MMSD_OK;
+  return components_to_host<real>(p, desc_of<real>(p).m[p->acc], m_out);
 }
 
 // normalize = false restores a checkpointed m bit for bit.
 template <typename real>
 int copy_m_to_device(mmsd_problem p, const double* m, bool normalize) {
   const Prob<real>& P = desc_of<real>(p);
-  const int N = p->A.N;
-  std::vector<real> tmp(3 * (size_t)N);
-  for (int i = 0; i < N; ++i) {
-    const double x = m[3 * (size_t)i], y = m[3 * (size_t)i + 1], z = m[3 * (size_t)i + 2];
-    const double n = std::sqrt(x * x + y * y + z * z);
-    if (!(n > 0) || !std::isfinite(n)) return invalid("zero or non-finite magnetization at node " + std::to_string(i));
-    const double s = normalize ? 1.0 / n : 1.0;
-    tmp[i] = (real)(normalize ? x / n : x * s);
-    tmp[(size_t)N + i] = (real)(normalize ? y / n : y * s);
-    tmp[2 * (size_t)N + i] = (real)(normalize ? z / n : z * s);
-  }
+  const int64_t N = p->A.N;
+  const size_t pitch = component_pitch<real>(p);
+  std::vector<real> tmp(3 * pitch);
+  std::atomic<int64_t> bad{N};   // the first node without a direction
+  over_nodes(N, [&](int64_t a, int64_t b) {
+    for (int64_t i = a; i < b; ++i) {
+      const double x = m[3 * i], y = m[3 * i + 1], z = m[3 * i + 2];
+      const double n = std::sqrt(x * x + y * y + z * z);
+      if (!(n > 0) || !std::isfinite(n)) {
+        for (int64_t at = bad.load(); i < at && !bad.compare_exchange_weak(at, i);) {
+        }
+        return;
+      }
+      tmp[i] = (real)(normalize ? x / n : x);
+      tmp[pitch + i] = (real)(normalize ? y / n : y);
+      tmp[2 * pitch + i] = (real)(normalize ? z / n : z);
+    }
+  });
+  if (bad.load() < N) return invalid("zero or non-finite magnetization at node " + std::to_string(bad.load()));
   hipStream_t st = p->ctx->stream;
-  for (int k = 0; k < 3; ++k)
-    MMSD_HIP(hipMemcpyAsync(P.m[p->acc][k], tmp.data() + (size_t)k * N, sizeof(real) * N, hipMemcpyHostToDevice, st));
+  MMSD_HIP(hipMemcpyAsync(P.m[p->acc][0], tmp.data(), sizeof(real) * (2 * pitch + N), hipMemcpyHostToDevice, st));
   MMSD_HIP(hipStreamSynchronize(st));
   p->h_valid = false;
   return MMSD_OK;
@@ -1093,6 +1145,8 @@ int mmsd_ctx_destroy(mmsd_ctx c) {
   (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->timing.pool) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->timing.pending) (void)hipEventDestroy(e);
+  for (hipEvent_t e : c->batch_ev)
+    if (e) (void)hipEventDestroy(e);
   if (c->own_stream) (void)hipStreamDestroy(c->stream);
   delete c;
   return MMSD_OK;
@@ -1209,6 +1263,7 @@ int mmsd_problem_create(mmsd_ctx c, const mmsd_mesh* mesh, const mmsd_material* 
   p->L = Csr{};
   p->Ldiag = std::vector<double>();
   if (rc) {
+    if (p->mirror) (void)hipHostFree(p->mirror);
     if (p->arena) c->dfree(p->arena);
     if (p->amg_arena) c->dfree(p->amg_arena);
     delete p;
@@ -1231,7 +1286,7 @@ int mmsd_problem_destroy(mmsd_problem p) {
   (void)hipSetDevice(c->device);
   (void)hipStreamSynchronize(c->stream);
   for (auto& kv : p->graphs) (void)hipGraphExecDestroy(kv.second);
-  if (p->hctrl) (void)hipHostFree(p->hctrl);
+  if (p->mirror) (void)hipHostFree(p->mirror);
   c->dfree(p->arena);
   if (p->amg_arena) c->dfree(p->amg_arena);
   delete p;
@@ -1335,24 +1390,8 @@ int mmsd_get_field(mmsd_problem p, double* h_out) {
   if (!p->h_valid) return invalid("no field stored: call mmsd_evaluate first");
   std::lock_guard<std::mutex> lk(p->ctx->mu);
   (void)hipSetDevice(p->ctx->device);
-  const int N = p->A.N;
-  hipStream_t st = p->ctx->stream;
-  std::vector<double> tmp(3 * (size_t)N);
-  for (int k = 0; k < 3; ++k) {
-    if (p->precision == MMSD_MIXED) {
-      std::vector<float> f(N);
-      MMSD_HIP(hipMemcpyAsync(f.data(), desc_of<float>(p).h[k], 4 * (size_t)N, hipMemcpyDeviceToHost, st));
-      MMSD_HIP(hipStreamSynchronize(st));
-      for (int i = 0; i < N; ++i) tmp[(size_t)k * N + i] = f[i];
-    } else {
-      MMSD_HIP(hipMemcpyAsync(tmp.data() + (size_t)k * N, desc_of<double>(p).h[k], 8 * (size_t)N,
-                              hipMemcpyDeviceToHost, st));
-    }
-  }
-  MMSD_HIP(hipStreamSynchronize(st));
-  for (int i = 0; i < N; ++i)
-    for (int k = 0; k < 3; ++k) h_out[3 * (size_t)i + k] = tmp[(size_t)k * N + i];
-  return MMSD_OK;
+  return p->precision == MMSD_MIXED ? components_to_host<float>(p, desc_of<float>(p).h, h_out)
+                                    : components_to_host<double>(p, desc_of<double>(p).h, h_out);
 }
 
 int mmsd_get_potential(mmsd_problem p, double* u_out) {
@@ -1526,7 +1565,6 @@ int mmsd_minimize_batch(mmsd_problem* probs, int n, const mmsd_options* o, mmsd_
     rc = hip_fail(hipGetLastError(), "pinned poll buffer");
   if (!rc && hipMemsetAsync(dndone, 0, 4, st) != hipSuccess) rc = hip_fail(hipGetLastError(), "memset");
   for (int i = 0; i < n && !rc; ++i) {
-    if ((rc = ensure_pinned(probs[i]))) break;
     rc = arm(probs[i], rs[i], ST_INIT, 0);
   }
   std::map<int, hipGraphExec_t> graphs;
@@ -1597,11 +1635,13 @@ int mmsd_minimize_batch(mmsd_problem* probs, int n, const mmsd_options* o, mmsd_
   int worst = MMSD_OK;
   for (int i = 0; i < n && !rc; ++i) {
     mmsd_problem p = probs[i];
-    if (hipMemcpy(&p->hctrl[0], p->dctrl, 2 * sizeof(Ctrl), hipMemcpyDeviceToHost) != hipSuccess) {
-      rc = hip_fail(hipGetLastError(), "batch result copy");
+    const Ctrl* done = outcome(p);
+    if (!done) {
+      set_error("a batched problem ended without a result");
+      rc = MMSD_E_HIP;
       break;
     }
-    const Ctrl& C = latest(&p->hctrl[0]);
+    const Ctrl& C = *done;
     p->acc = C.acc;
     p->ucur = C.ucur;
     p->h_valid = false;

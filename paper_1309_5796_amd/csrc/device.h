@@ -85,7 +85,8 @@ struct Ctrl {
   // stagnation test of the chain mode: energy and torque at the last
   // progress, FP32 resolution of the energy, accepted steps since
   double prog_e, prog_T, e_res;
-  int stall, pad3;
+  int stall;
+  int run;                       // number of the run (Mirror::run once it is done)
   // potential buffers (indices into u3): the working one, the accepted
   // state's, and the two a PREP starts from (u_src2 < 0: u_src alone; else
   // the interpolation u_src + rho (u_src2 - u_src) after a rejected trial)
@@ -107,6 +108,14 @@ struct Ctrl {
   double pad1[4];
 };
 static_assert(sizeof(Ctrl) % 8 == 0, "Ctrl is copied as 8-byte words");
+
+// Pinned host memory of one problem: the launch in which a run finishes
+// writes the final control state here, then the run's number, so that the
+// host learns the outcome without a copy between its launches.
+struct Mirror {
+  Ctrl ctrl;
+  int run, pad;
+};
 
 // One level of the multigrid hierarchy (level 0 is the potential matrix).
 // wd = w / diag, w the V-cycle smoother's damped-Jacobi weight.
@@ -224,6 +233,7 @@ struct ProbT {
   Ptr<Pair<real>> rq;         // of the current iteration: {r, q} (level 0 fused) or {wd r, wd q}
   Ptr<real> q;                // L p (level 0 unfused)
   Ptr<const double> btab;     // algorithmic bytes per executed phase, indexed by byte_slot()
+  Ptr<Mirror> mirror;         // host memory
   // reductions and control
   Ptr<unsigned> ndone;        // nullable: incremented once when the problem finishes
   Ptr<int> done_list;         // nullable: receives `slot` at position ndone - 1

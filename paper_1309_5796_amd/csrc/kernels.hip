@@ -1457,7 +1457,16 @@ __global__ void __launch_bounds__(kBlock, 4) k_step(const ProbDev<real>* __restr
     __syncthreads();
     if (lb == 0) {
       publish();
-      if (threadIdx.x == 0 && s_newly_done) signal_done<real>(P, &s_c);
+      if (s_newly_done) {   // once per run
+        if (threadIdx.x == 0) signal_done<real>(P, &s_c);
+        const long long* src = reinterpret_cast<const long long*>(&s_c);
+        DevPtr<long long> dst = reinterpret_cast<DevPtr<long long>>(&P.mirror->ctrl);
+        for (int w = threadIdx.x; w < (int)(sizeof(Ctrl) / 8); w += kBlock) dst[w] = src[w];
+        __threadfence_system();   // each thread's words before the number below
+        __syncthreads();
+        if (threadIdx.x == 0)
+          __hip_atomic_store(&P.mirror->run, s_c.run, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
     }
     phase = s_c.phase;
     mop = s_c.mg_op;
@@ -1501,7 +1510,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_step(const ProbDev<real>* __restr
 // above both slots' so the host always picks the newest.
 struct CtrlInit {
   int stage, terms, nonmono_M, step_rule, pcg_maxit, store_h, demag, acc, precond, chain, max_halvings, stop_sum2;
-  int ucur, pad;
+  int ucur, run;
   long long max_evals;
   double tol, pcg_rtol2, c1, rho, kappa0, theta0, tau_min, tau_max, tau_floor, e_res;
   double bz[3], c_an, vol;
@@ -1532,6 +1541,7 @@ __global__ void k_ctrl_init(Ctrl* ctrl, int slot, CtrlInit a) {
   C->store_h = a.store_h;
   C->demag = a.demag;
   C->stop_sum2 = a.stop_sum2;
+  C->run = a.run;
   C->ucur = C->uacc = C->u_src = a.ucur;
   C->u_src2 = -1;
   C->u_w = 0.0;
@@ -1611,11 +1621,11 @@ template hipError_t launch_step<float>(int, const Prob<float>*, int, const int*,
 
 hipError_t launch_ctrl_init(Ctrl* ctrl, int slot, int stage, int terms, int nonmono_M, int step_rule,
                             int pcg_maxit, int store_h, int demag, int acc, int precond, int chain,
-                            int max_halvings, int stop_sum2, int ucur, long long max_evals,
+                            int max_halvings, int stop_sum2, int ucur, int run, long long max_evals,
                             const double* dparams, hipStream_t s) {
   CtrlInit a;
   a.ucur = ucur;
-  a.pad = 0;
+  a.run = run;
   a.precond = precond;
   a.chain = chain;
   a.max_halvings = max_halvings;

@@ -33,7 +33,7 @@ hipError_t launch_step(int lpr, const Prob<real>* probs, int nprob, const int* b
                        hipStream_t s);
 hipError_t launch_ctrl_init(Ctrl* ctrl, int slot, int stage, int terms, int nonmono_M, int step_rule,
                             int pcg_maxit, int store_h, int demag, int acc, int precond, int chain,
-                            int max_halvings, int stop_sum2, int ucur, long long max_evals,
+                            int max_halvings, int stop_sum2, int ucur, int run, long long max_evals,
                             const double* dparams, hipStream_t s);
 
 hipError_t launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t s);
@@ -106,7 +106,6 @@ int resolve(mmsd_problem_s* p, const mmsd_options* o, Resolved* r);
 int arm(mmsd_problem_s* p, const Resolved& r, int stage, int store_h);
 int launch_table(const Table& t, int parity, hipStream_t st);
 void fill_result(mmsd_problem_s* p, const Ctrl& C, mmsd_result* out, double secs, int64_t launches);
-int ensure_pinned(mmsd_problem_s* p);
 int issue(mmsd_ctx_s* c, const std::vector<Table>& tabs, int B, std::map<int, hipGraphExec_t>* graphs);
 int batch_blocks(mmsd_problem_s* p, bool demag);
 double run_bytes(mmsd_problem_s* p, const Ctrl& C);
@@ -125,6 +124,7 @@ struct mmsd_ctx_s {
   int assembly = MMSD_ASSEMBLE_HOST;                     // where new problems' operators are assembled
   bool use_graph = true;
   mmsd::TimingState timing;
+  hipEvent_t batch_ev[2] = {nullptr, nullptr};   // the batches of launches in flight
   std::map<int64_t, std::pair<int, int>> tuned;   // autotuner results by problem class
   std::mutex mu;            // serializes device work issued through this context
   void* dalloc(size_t bytes);
@@ -163,8 +163,9 @@ struct mmsd_problem_s {
   bool amg_folded = false;                // the last DOWN forms the coarsest solution (Ainv M)
   char* amg_arena = nullptr;
   size_t amg_bytes = 0;
-  mmsd::Ctrl* hctrl = nullptr;            // pinned mirrors [2 polls][2 slots]
+  mmsd::Mirror* mirror = nullptr;         // pinned: the outcome of the last run
+  mmsd::Ctrl* hpoll = nullptr;            // pinned: both control slots, read now and then during a long run
+  int run = 0;                            // number of the last run armed
   std::map<int, hipGraphExec_t> graphs;   // batch size -> instantiated graph
-  int64_t last_launches = 0;
   double setup_t[4] = {0, 0, 0, 0};       // creation: assembly, multigrid setup, device build, total (s)
 };

@@ -201,8 +201,7 @@ void mmsd_server_s::setup_loop() {
     if (!rc) r->demag = (res.terms & MMSD_DEMAG) != 0;
     if (!rc) {
       std::lock_guard<std::mutex> g(upload_ctx->mu);
-      rc = ensure_pinned(p);
-      if (!rc) rc = arm(p, res, ST_INIT, 0);
+      rc = arm(p, res, ST_INIT, 0);
       if (!rc && hipStreamSynchronize(upload_ctx->stream) != hipSuccess) rc = MMSD_E_HIP;
     }
     if (rc) r->error = mmsd_last_error();
