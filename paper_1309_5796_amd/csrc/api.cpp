@@ -155,17 +155,22 @@ static int row_lanes(int64_t n, double avg) {
 // a launch (about 2 round trips) and the residual's way through memory but
 // has about 3 (finest level) to 6 times R's entries, so the cost of a sweep
 // is the larger of its round trips over a full launch's 512 blocks and its
-// bytes, a round trip being worth about 3.5 MB at the rate a sweep of large
-// matrices reaches.  On the finest level that draws the line near 150,000
-// rows: with M the 20 nm cube's iteration loses one of six launches, while
-// the 80 nm cube's grows from 67.1 to 70.0 us (PCG_B with M 18.5 us against
+// bytes, entries and gathers, a round trip being worth about 3.5 MB at the
+// rate a sweep of large matrices reaches.  On the finest level M's rows gather
+// scattered {r, q} records, counted as 8 values each, which draws the line
+// near 20,000 rows: with M the 20 nm cube's iteration loses one of six
+// launches (evaluation 1.18 -> 1.08 ms); the 132,651-row ball alone would
+// still gain 2% (16 evaluations 19.65 -> 19.2 ms), but 14 grains of 13k to
+// 110k rows in one batch lose 6% (60.6 -> 64.3 ms), and the 80 nm cube's
+// iteration grows from 67.1 to 70.0 us (PCG_B with M 18.5 us against
 // 10.1 + 9.0 us for PCG_B and REST, POST with A 14.0 against 11.1 us).
 constexpr double kTripBytes = 3.5e6;
-static bool fuse_restriction(int64_t n, int64_t nR, double avgR, double avgM, size_t s) {
-  auto cost = [&](double avg) {
-    return std::max((double)sweep_cost(nR, avg, row_lanes(nR, avg)), (4 + s) * avg * (double)nR / kTripBytes);
+static bool fuse_restriction(int64_t n, int64_t nR, double avgR, double avgM, size_t s, bool finest) {
+  auto cost = [&](double avg, size_t gather) {
+    return std::max((double)sweep_cost(nR, avg, row_lanes(nR, avg)),
+                    (4 + s + gather) * avg * (double)nR / kTripBytes);
   };
-  return cost(avgM) < cost(avgR) + 2 + 2.0 * s * n / kTripBytes;
+  return cost(avgM, finest ? 8 * s : s) < cost(avgR, s) + 2 + 2.0 * s * n / kTripBytes;
 }
 
 // Largest dense Ainv M (coarsest size x last level's rows) folded into the
@@ -345,7 +350,7 @@ int build_amg(mmsd_problem p) {
     Csr Q = smoothed_prolongation(L);
     const double nn = std::max(1, L.P.ncols);
     fused[l] = (c->vcycle & MMSD_VC_FUSE_REST) &&
-               fuse_restriction(L.A.nrows, L.P.ncols, L.P.ci.size() / nn, Q.ci.size() / nn, s);
+               fuse_restriction(L.A.nrows, L.P.ncols, L.P.ci.size() / nn, Q.ci.size() / nn, s, l == 0);
     if (fused[l]) {
       M = residual_restriction(L);
       Q = fused_post_smoothing(L, Q);
@@ -714,16 +719,29 @@ int arm(mmsd_problem p, const Resolved& r, int stage, int store_h) {
   return MMSD_OK;
 }
 
-int launch_table(const Table& t, int parity, hipStream_t st) {
-  hipError_t e =
-      t.precision == MMSD_MIXED
-          ? launch_step<float>(t.lpr, (const Prob<float>*)t.dprobs, t.nprob, t.dblk, t.grid, parity, st)
-          : launch_step<double>(t.lpr, (const Prob<double>*)t.dprobs, t.nprob, t.dblk, t.grid, parity, st);
-  if (e != hipSuccess) return hip_fail(e, "step launch");
-  return MMSD_OK;
+int launches_per_tick(const std::vector<Table>& tabs) {
+  return tabs.size() == 2 && tabs[0].lpr == tabs[1].lpr ? 1 : (int)tabs.size();
 }
 
-// Issue B ticks (one launch per table per tick), through a cached graph
+// One step of every problem: a launch per table, or one for a table of each
+// precision.
+static int launch_tick(const std::vector<Table>& tabs, int parity, hipStream_t st) {
+  hipError_t e = hipSuccess;
+  if (launches_per_tick(tabs) < (int)tabs.size()) {
+    const Table &d = tabs[0], &f = tabs[1];
+    e = launch_both(d.lpr, (const Prob<double>*)d.dprobs, d.nprob, d.dblk, d.grid, (const Prob<float>*)f.dprobs,
+                    f.nprob, f.dblk, f.grid, parity, st);
+  } else {
+    for (const Table& t : tabs)
+      if (e == hipSuccess)
+        e = t.precision == MMSD_MIXED
+                ? launch_step<float>(t.lpr, (const Prob<float>*)t.dprobs, t.nprob, t.dblk, t.grid, parity, st)
+                : launch_step<double>(t.lpr, (const Prob<double>*)t.dprobs, t.nprob, t.dblk, t.grid, parity, st);
+  }
+  return e == hipSuccess ? MMSD_OK : hip_fail(e, "step launch");
+}
+
+// Issue B ticks (launches_per_tick launches each), through a cached graph
 // when allowed and timing is off.
 int issue(mmsd_ctx c, const std::vector<Table>& tabs, int B, std::map<int, hipGraphExec_t>* graphs) {
   hipStream_t st = c->stream;
@@ -750,9 +768,7 @@ int issue(mmsd_ctx c, const std::vector<Table>& tabs, int B, std::map<int, hipGr
     if (it == graphs->end()) {
       hipGraph_t g;
       MMSD_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-      for (int b = 0; b < B && !rc; ++b)
-        for (const Table& t : tabs)
-          if (!rc) rc = launch_table(t, b & 1, st);
+      for (int b = 0; b < B && !rc; ++b) rc = launch_tick(tabs, b & 1, st);
       hipError_t ec = hipStreamEndCapture(st, &g);
       if (rc) return rc;
       if (ec != hipSuccess) return hip_fail(ec, "hipStreamEndCapture");
@@ -764,16 +780,14 @@ int issue(mmsd_ctx c, const std::vector<Table>& tabs, int B, std::map<int, hipGr
     }
     MMSD_HIP(hipGraphLaunch(it->second, st));
   } else {
-    for (int b = 0; b < B && !rc; ++b)
-      for (const Table& t : tabs)
-        if (!rc) rc = launch_table(t, b & 1, st);
+    for (int b = 0; b < B && !rc; ++b) rc = launch_tick(tabs, b & 1, st);
     if (rc) return rc;
   }
   if (T.stride > 0) {
     MMSD_HIP(hipEventRecord(e1, st));
     T.pending.push_back(e0);
     T.pending.push_back(e1);
-    T.pending_launches.push_back((double)B * (double)tabs.size());
+    T.pending_launches.push_back((double)B * launches_per_tick(tabs));
   }
   return MMSD_OK;
 }

@@ -31,6 +31,10 @@ int hip_fail(hipError_t e, const char* what);
 template <typename real>
 hipError_t launch_step(int lpr, const Prob<real>* probs, int nprob, const int* blk_start, int grid, int parity,
                        hipStream_t s);
+// The same for a table of each precision in one launch.
+hipError_t launch_both(int lpr, const Prob<double>* probs_d, int nprob_d, const int* blk_start_d, int grid_d,
+                       const Prob<float>* probs_f, int nprob_f, const int* blk_start_f, int grid_f, int parity,
+                       hipStream_t s);
 hipError_t launch_ctrl_init(Ctrl* ctrl, int slot, int stage, int terms, int nonmono_M, int step_rule,
                             int pcg_maxit, int store_h, int demag, int acc, int precond, int chain,
                             int max_halvings, int stop_sum2, int ucur, int run, long long max_evals,
@@ -104,7 +108,7 @@ struct mmsd_problem_s;
 namespace mmsd {
 int resolve(mmsd_problem_s* p, const mmsd_options* o, Resolved* r);
 int arm(mmsd_problem_s* p, const Resolved& r, int stage, int store_h);
-int launch_table(const Table& t, int parity, hipStream_t st);
+int launches_per_tick(const std::vector<Table>& tabs);
 void fill_result(mmsd_problem_s* p, const Ctrl& C, mmsd_result* out, double secs, int64_t launches);
 int issue(mmsd_ctx_s* c, const std::vector<Table>& tabs, int B, std::map<int, hipGraphExec_t>* graphs);
 int batch_blocks(mmsd_problem_s* p, bool demag);

@@ -346,7 +346,7 @@ void mmsd_server_s::device_loop() {
     if (!rc && hipStreamSynchronize(st) != hipSuccess) rc = MMSD_E_HIP;
     lk.lock();
     loop_seconds += std::chrono::duration<double>(Clock::now() - t_batch).count();
-    launches += B * tabs.size();
+    launches += B * launches_per_tick(tabs);
     if (rc) {
       // a device failure poisons every resident request
       for (Request* r : resident) {
