@@ -292,11 +292,16 @@ __device__ __forceinline__ Acc l_row(const ProbDev<real>& P, int i, G&& g) {
 }
 
 // ---- PREP: trial magnetization, Poisson right-hand side, initial residual ----
-// Over the block's chunk of rows, first the magnet rows with LPR lanes per
-// row: the trial m_t (Cayley step, also recomputed at magnet neighbours) and
-// b = D1 m_t, stored in the residual slot; then every potential row, one
-// thread per row over the sliced matrix: r = b - L u.  The block barrier
-// between the two orders each row's b before its reuse (same block).
+// First the block's magnet rows with LPR lanes per row: the trial m_t (Cayley
+// step, also recomputed at magnet neighbours) and b = D1 m_t, stored in the
+// residual slot; then, one thread per row over the sliced matrix, r = b - L u
+// on the same rows and on the block's share of the others.  The block barrier
+// between the two orders each row's b before its reuse (same block).  The
+// magnet rows (the first N) and the others are dealt to the blocks
+// separately: they are bound by the chain of loads of the divergence, and
+// chunks of all rows together gave the 27% (80 nm cube) to 48% (polycrystal)
+// magnet rows to as many of the blocks, with one neighbour in flight per
+// lane (the phase took 51 and 453 us there and takes 34 and 254 us).
 template <typename real, int LPR>
 __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, double* acc) {
   constexpr int RPP = kBlock / LPR;
@@ -304,9 +309,12 @@ __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, doubl
   const int slot = threadIdx.x / LPR;
   const bool demag = C->demag != 0;
   const bool amg = C->precond == PC_AMG;
-  const int R = demag ? P.Nt : P.N;
+  constexpr int kU = kUnrollWide<real>;
+  // rows 0 .. Nm - 1 (the magnet rows and what completes their last slice)
+  // and Nm .. Nt - 1
+  const int Nm = demag ? min(P.Nt, (P.N + 63) & ~63) : P.N;
   int r0, r1, rs;
-  chunk_rows(R, P.G, blk, kBlock, 64, r0, r1, rs);
+  chunk_rows(Nm, P.G, blk, kBlock, 64, r0, r1, rs);
   const int a = C->acc, tr = 1 - a;
   const real ht = real(0.5 * C->tau);
   DevPtr<const real> __restrict__ max_ = P.m[a][0];
@@ -333,11 +341,34 @@ __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, doubl
       }
       if (demag) {
         const int k1 = P.mrp[i + 1];
-        for (int k = P.mrp[i] + lane; k < k1; k += LPR) {
-          const int j = P.mci[k];
-          real ox, oy, oz;
-          cayley<real>(max_[j], may[j], maz[j], Hax[j], Hay[j], Haz[j], ht, ox, oy, oz);
-          bi += (double)P.D1[0][k] * ox + (double)P.D1[1][k] * oy + (double)P.D1[2][k] * oz;
+        for (int k0 = P.mrp[i] + lane; k0 < k1; k0 += kU * LPR) {
+          int j[kU];
+          real dx[kU], dy[kU], dz[kU];
+#pragma unroll
+          for (int u = 0; u < kU; ++u) {
+            const bool ok = k0 + u * LPR < k1;
+            const int k = ok ? k0 + u * LPR : k0;
+            j[u] = P.mci[k];
+            dx[u] = ok ? P.D1[0][k] : real(0);
+            dy[u] = ok ? P.D1[1][k] : real(0);
+            dz[u] = ok ? P.D1[2][k] : real(0);
+          }
+          real gm[kU][3], gH[kU][3];
+#pragma unroll
+          for (int u = 0; u < kU; ++u) {
+            gm[u][0] = max_[j[u]];
+            gm[u][1] = may[j[u]];
+            gm[u][2] = maz[j[u]];
+            gH[u][0] = Hax[j[u]];
+            gH[u][1] = Hay[j[u]];
+            gH[u][2] = Haz[j[u]];
+          }
+#pragma unroll
+          for (int u = 0; u < kU; ++u) {
+            real ox, oy, oz;
+            cayley<real>(gm[u][0], gm[u][1], gm[u][2], gH[u][0], gH[u][1], gH[u][2], ht, ox, oy, oz);
+            bi += (double)dx[u] * ox + (double)dy[u] * oy + (double)dz[u] * oz;
+          }
         }
       }
     }
@@ -362,9 +393,7 @@ __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, doubl
   const bool interp = C->u_src2 >= 0;
   const real wr = real(C->u_w);
   auto u_at = [&](int j) -> real { return interp ? ua[j] + wr * (ub[j] - ua[j]) : ua[j]; };
-  for (int base = r0; base < r1; base += rs) {
-    const int i = base + threadIdx.x;
-    if (i >= r1) continue;
+  auto residual = [&](int i) {
     const real bi = i < P.N ? (amg ? r2[i] : rec[i].r) : real(0);
     const real ui = u_at(i);
     uw[i] = ui;
@@ -387,7 +416,12 @@ __device__ void phase_prep(const ProbDev<real>& P, const Ctrl* C, int blk, doubl
     acc[0] += (double)bi * (double)bi;
     acc[1] += (double)ri * (double)ri;
     acc[2] += (double)ri * (double)ui;
-  }
+  };
+  for (int base = r0; base < r1; base += rs)
+    if (base + (int)threadIdx.x < r1) residual(base + threadIdx.x);
+  chunk_rows(P.Nt - Nm, P.G, blk, kBlock, 64, r0, r1, rs);
+  for (int base = r0; base < r1; base += rs)
+    if (base + (int)threadIdx.x < r1) residual(Nm + base + threadIdx.x);
 }
 
 // ---- CG0: w = L D^-1 r for the starting residual (one thread per row) ----
