@@ -188,13 +188,15 @@ struct Sliced {
   std::vector<int> order;   // row at each position (empty: position = row)
 };
 
-// Rows sorted by length, longest first, inside windows of kOrderWindow rows
-// (8 slices): a slice is as wide as its longest row, and the multigrid's
-// matrices mix row lengths (aggregates of 5-47 fine nodes, rows of A P next
-// to aggregate boundaries), so that sorting cuts the padding (polycrystal:
-// R_0 1.34x -> 1.06x its entries, A P 1.16x -> 1.03x) while rows stay
-// inside their neighbourhood for the gathers and the XCD chunks.
-constexpr int kOrderWindow = 512;
+// Rows sorted by length, longest first, inside windows of kOrderWindow rows:
+// a slice is as wide as its longest row, and the multigrid's matrices mix row
+// lengths (aggregates of 5-47 fine nodes, rows of A P next to aggregate
+// boundaries), so that sorting cuts the padding.  But neighbouring lanes then
+// hold rows further apart, whose gathers and own values share fewer cache
+// lines: with windows of 512 rows the polycrystal's post-smoothing of the
+// finest level took 84 us, with 256 82.6 us, with 128 76.8 us, within a slice
+// 77.7 us, its 14 evaluations 157.4, 155.1, 152.2 and 153.1 ms.
+constexpr int kOrderWindow = 128;
 std::vector<int> window_order(const std::vector<int>& len) {
   const int64_t n = (int64_t)len.size();
   std::vector<int> order(n);
