@@ -497,7 +497,14 @@ int build_amg(mmsd_problem p) {
   return MMSD_OK;
 }
 
-constexpr double kStreamBytes = 128.0 * (1 << 20);
+// Size of the sliced potential matrix from which every sliced matrix is read
+// past the caches (non-temporally): the solve then moves several times the
+// 256 MB Infinity Cache per iteration.  Measured around the line, 8
+// evaluations of a polycrystal with the hint against without: FP64 0.72M rows
+// (57 MB) 35.5 / 35.7 ms, 1.11M rows (89 MB) 47.0 / 48.5, 1.53M rows (122 MB)
+// 62.7 / 66.1; mixed 1.53M rows (82 MB) 27.5 / 28.4; but FP64 0.50M rows
+// (40 MB) 30.7 / 27.5 and mixed 0.72M rows (39 MB) 17.1 / 15.8.
+constexpr double kStreamBytes = 64.0 * (1 << 20);
 
 // The problem's device arena: operators, node state, control.  With D the
 // operators come from the device assembly's buffers (converted on the
@@ -590,8 +597,6 @@ int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
   P.N = (int)N;
   P.Nt = (int)Nt;
   P.G = G;
-  // stream the sliced matrices past the caches when the potential matrix
-  // alone exceeds half of the 256 MB Infinity Cache
   P.stream = (double)nnzLs * (4 + sizeof(real)) > kStreamBytes ? 1 : 0;
   P.blk0 = 0;
   P.mrp = (const int*)(base + L.mrp);

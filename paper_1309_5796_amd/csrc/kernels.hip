@@ -200,10 +200,11 @@ __device__ __forceinline__ void chunk_rows(int R, int G, int blk, int rpp, int a
 }
 
 // Matrix entries of the sliced sweeps are read once per sweep.  On problems
-// whose potential matrix exceeds the Infinity Cache they are streamed with the
+// whose matrices exceed the Infinity Cache they are streamed with the
 // non-temporal hint (nt), so that they do not push the gathered vectors and
-// the coarse levels' data out of the L2 (polycrystal: -6% per launch); on
-// smaller ones, which the Infinity Cache holds, the plain loads are faster.
+// the coarse levels' data out of the L2 (14 evaluations of the polycrystal
+// 169.5 ms without, 156.9 with); on smaller ones, which the Infinity Cache
+// holds, the plain loads are faster.
 template <bool NT, typename T>
 __device__ __forceinline__ T stream_ld(DevPtr<const T> p, int i) {
   if constexpr (NT) return __builtin_nontemporal_load(p + i);
