@@ -35,12 +35,13 @@ thread_local const std::atomic<int>* t_sharing = nullptr;
 
 void share_cores(const std::atomic<int>* active) { t_sharing = active; }
 
-void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& f) {
+void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& f, int64_t grain) {
   unsigned hw = std::thread::hardware_concurrency();
   int nt = (int)std::max<unsigned>(1, std::min<unsigned>(hw ? hw : 4, 16));
   if (t_sharing) nt = std::max(1, std::min(nt, (int)(hw ? hw : 4) / std::max(1, t_sharing->load())));
-  if (n < 2048) nt = 1;
-  if (nt == 1) {
+  if (grain > 0) nt = (int)std::min<int64_t>(nt, (n + grain - 1) / grain);
+  else if (n < 2048) nt = 1;
+  if (nt <= 1) {
     f(0, n);
     return;
   }
@@ -51,6 +52,25 @@ void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& f) {
     if (a < b) th.emplace_back(f, a, b);
   }
   for (auto& x : th) x.join();
+}
+
+Csr transpose(const Csr& M) {
+  Csr T;
+  T.nrows = M.ncols;
+  T.ncols = M.nrows;
+  T.rp.assign(T.nrows + 1, 0);
+  for (int c : M.ci) T.rp[c + 1]++;
+  for (int i = 0; i < T.nrows; ++i) T.rp[i + 1] += T.rp[i];
+  T.ci.resize(M.ci.size());
+  T.v.resize(M.v.size());
+  std::vector<int> fill(T.rp.begin(), T.rp.end() - 1);
+  for (int i = 0; i < M.nrows; ++i)
+    for (int k = M.rp[i]; k < M.rp[i + 1]; ++k) {
+      const int pos = fill[M.ci[k]]++;
+      T.ci[pos] = i;
+      T.v[pos] = M.v[k];
+    }
+  return T;   // rows come out with ascending columns
 }
 
 namespace {
@@ -150,25 +170,6 @@ int aggregate(const Csr& A, const std::vector<double>& d, double theta, std::vec
     ++na;
   }
   return na;
-}
-
-Csr transpose(const Csr& M) {
-  Csr T;
-  T.nrows = M.ncols;
-  T.ncols = M.nrows;
-  T.rp.assign(T.nrows + 1, 0);
-  for (int c : M.ci) T.rp[c + 1]++;
-  for (int i = 0; i < T.nrows; ++i) T.rp[i + 1] += T.rp[i];
-  T.ci.resize(M.ci.size());
-  T.v.resize(M.v.size());
-  std::vector<int> fill(T.rp.begin(), T.rp.end() - 1);
-  for (int i = 0; i < M.nrows; ++i)
-    for (int k = M.rp[i]; k < M.rp[i + 1]; ++k) {
-      const int pos = fill[M.ci[k]]++;
-      T.ci[pos] = i;
-      T.v[pos] = M.v[k];
-    }
-  return T;   // rows come out with ascending columns
 }
 
 // C = A B (Gustavson, rows in parallel, sorted columns).  Each thread fills
@@ -284,14 +285,14 @@ Csr without_zero_couplings(const std::vector<int>& rp, const std::vector<int>& c
     for (int64_t i = a; i < b; ++i)
       for (int k = rp[i]; k < rp[i + 1]; ++k)
         if (ci[k] == i) d[i] = v[k];
-  });
+  }, kLight);
   auto kept = [&](int64_t i, int k) {
     return ci[k] == i || !(std::fabs(v[k]) <= kZeroCoupling * std::fmin(d[i], d[ci[k]]));
   };
   parallel_for(n, [&](int64_t a, int64_t b) {
     for (int64_t i = a; i < b; ++i)
       for (int k = rp[i]; k < rp[i + 1]; ++k) Z.rp[i + 1] += kept(i, k);
-  });
+  }, kLight);
   for (int i = 0; i < n; ++i) Z.rp[i + 1] += Z.rp[i];
   Z.ci.resize(Z.rp[n]);
   Z.v.resize(Z.rp[n]);
@@ -304,45 +305,8 @@ Csr without_zero_couplings(const std::vector<int>& rp, const std::vector<int>& c
           Z.v[o++] = v[k];
         }
     }
-  });
+  }, kLight);
   return Z;
-}
-
-Csr residual_restriction(const AmgLevel& L) {
-  const Csr T = transpose(L.AP);   // (A P)^T: n_next x n
-  const Csr& R = L.R;
-  Csr M;
-  M.nrows = T.nrows;
-  M.ncols = T.ncols;
-  M.rp.assign(M.nrows + 1, 0);
-  // rows are the sorted unions of T's and R's rows: count, then fill
-  auto merge = [&](int I, int* ci, double* v) {
-    int a = T.rp[I], b = R.rp[I], o = 0;
-    const int ae = T.rp[I + 1], be = R.rp[I + 1];
-    while (a < ae || b < be) {
-      const int ca = a < ae ? T.ci[a] : INT32_MAX, cb = b < be ? R.ci[b] : INT32_MAX;
-      const int c = std::min(ca, cb);
-      double x = 0;
-      if (cb == c) x += R.v[b++];
-      if (ca == c) x -= T.v[a++] * L.wsmooth * L.dinv[c];
-      if (ci) {
-        ci[o] = c;
-        v[o] = x;
-      }
-      ++o;
-    }
-    return o;
-  };
-  parallel_for(M.nrows, [&](int64_t a, int64_t b) {
-    for (int64_t I = a; I < b; ++I) M.rp[I + 1] = merge((int)I, nullptr, nullptr);
-  });
-  for (int I = 0; I < M.nrows; ++I) M.rp[I + 1] += M.rp[I];
-  M.ci.resize(M.rp[M.nrows]);
-  M.v.resize(M.rp[M.nrows]);
-  parallel_for(M.nrows, [&](int64_t a, int64_t b) {
-    for (int64_t I = a; I < b; ++I) merge((int)I, &M.ci[M.rp[I]], &M.v[M.rp[I]]);
-  });
-  return M;
 }
 
 Csr smoothed_prolongation(const AmgLevel& L) {
@@ -371,15 +335,17 @@ Csr smoothed_prolongation(const AmgLevel& L) {
   };
   parallel_for(T.nrows, [&](int64_t a, int64_t b) {
     for (int64_t i = a; i < b; ++i) T.rp[i + 1] = merge((int)i, nullptr, nullptr);
-  });
+  }, kLight);
   for (int i = 0; i < T.nrows; ++i) T.rp[i + 1] += T.rp[i];
   T.ci.resize(T.rp[T.nrows]);
   T.v.resize(T.rp[T.nrows]);
   parallel_for(T.nrows, [&](int64_t a, int64_t b) {
     for (int64_t i = a; i < b; ++i) merge((int)i, &T.ci[T.rp[i]], &T.v[T.rp[i]]);
-  });
+  }, kLight);
   return T;
 }
+
+Csr residual_restriction(const AmgLevel& L) { return transpose(smoothed_prolongation(L)); }
 
 Csr fused_post_smoothing(const AmgLevel& L, const Csr& T) {
   const int n = L.A.nrows;
@@ -403,7 +369,7 @@ Csr fused_post_smoothing(const AmgLevel& L, const Csr& T) {
         C.v[o] = T.v[k];
       }
     }
-  });
+  }, kLight);
   return C;
 }
 

@@ -176,6 +176,9 @@ static bool fuse_restriction(int64_t n, int64_t nR, double avgR, double avgM, si
 // Largest dense Ainv M (coarsest size x last level's rows) folded into the
 // last DOWN.
 constexpr double kMaxFoldedBytes = 64.0 * (1 << 20);
+// Multiply-adds per thread at least, of the product Ainv M (a thread starts
+// in about 0.1 ms).
+constexpr int64_t kFoldGrain = 1 << 17;
 
 // A CSR matrix in slices of one wavefront, W lanes per row (1: 64 rows per
 // slice): slice s starts at so[s] and is as wide as its longest row; entry k
@@ -207,7 +210,7 @@ std::vector<int> window_order(const std::vector<int>& len) {
       auto last = order.begin() + std::min<int64_t>(n, (w + 1) * kOrderWindow);
       std::stable_sort(first, last, [&](int x, int y) { return len[x] > len[y]; });
     }
-  });
+  }, kLight / kOrderWindow);
   return order;
 }
 // Offsets of the slices of a CSR pattern (W lanes per row).
@@ -220,7 +223,7 @@ std::vector<int> slice_offsets(const std::vector<int>& rp, int W = 1) {
       for (int64_t i = rows * sl; i < std::min<int64_t>(n, rows * (sl + 1)); ++i) w = std::max(w, rp[i + 1] - rp[i]);
       so[sl + 1] = 64 * ((w + W - 1) / W);
     }
-  });
+  }, kLight / rows);
   for (int64_t sl = 0; sl < ns; ++sl) so[sl + 1] += so[sl];
   return so;
 }
@@ -228,6 +231,7 @@ std::vector<int> slice_offsets(const std::vector<int>& rp, int W = 1) {
 Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci, const std::vector<double>& v,
                    int ncols, int W = 1, bool ordered = false) {
   const int64_t n = (int64_t)rp.size() - 1, rows = 64 / W, ns = (n + rows - 1) / rows;
+  const int lw = std::ilogb(W);   // W is a power of two
   Sliced S;
   if (ordered) {
     std::vector<int> len(n);
@@ -249,7 +253,7 @@ Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci, const
         const int64_t i = pos < n && ordered ? S.order[pos] : pos;
         const int len = pos < n ? rp[i + 1] - rp[i] : 0;
         for (int k = 0; k < w * W; ++k) {
-          const int64_t q = S.so[sl] + 64LL * (k / W) + r * W + k % W;
+          const int64_t q = S.so[sl] + 64LL * (k >> lw) + r * W + (k & (W - 1));
           if (k < len) {
             S.sc[q] = ci[rp[i] + k];
             S.sv[q] = v[rp[i] + k];
@@ -259,7 +263,7 @@ Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci, const
         }
       }
     }
-  });
+  }, kLight / rows);
   return S;
 }
 
@@ -354,7 +358,7 @@ int build_amg(mmsd_problem p) {
     fused[l] = (c->vcycle & MMSD_VC_FUSE_REST) &&
                fuse_restriction(L.A.nrows, L.P.ncols, L.P.ci.size() / nn, Q.ci.size() / nn, s, l == 0);
     if (fused[l]) {
-      M = residual_restriction(L);
+      M = transpose(Q);   // residual_restriction(L)
       Q = fused_post_smoothing(L, Q);
       p->amg_m_nnz[l] = (int64_t)M.ci.size();
     }
@@ -377,6 +381,8 @@ int build_amg(mmsd_problem p) {
     const Csr& Ml = M;
     const int64_t nlast = H.lv[nl - 1].A.nrows;
     ainv_m.assign((size_t)H.nc * nlast, 0.0);
+    // few rows, each a whole pass over M: threads by work, not by rows (on one
+    // thread this was 4.2 of 10.3 ms of a 15,625-row hierarchy's device setup)
     parallel_for(H.nc, [&](int64_t I0, int64_t I1) {
       for (int64_t I = I0; I < I1; ++I) {
         double* out = &ainv_m[(size_t)I * nlast];
@@ -385,7 +391,7 @@ int build_amg(mmsd_problem p) {
           for (int k = Ml.rp[K]; k < Ml.rp[K + 1]; ++k) out[Ml.ci[k]] += a * Ml.v[k];
         }
       }
-    });
+    }, std::max<int64_t>(1, kFoldGrain / std::max<int64_t>(1, (int64_t)Ml.ci.size())));
     p->amg_folded = true;
     sl[nl - 1][2] = Sliced{};   // M itself is not swept then
   }
