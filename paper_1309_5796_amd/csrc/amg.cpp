@@ -31,6 +31,14 @@ namespace mmsd {
 
 namespace {
 thread_local const std::atomic<int>* t_sharing = nullptr;
+
+// Started threads, joined when the scope is left, by an exception too.
+struct Threads {
+  std::vector<std::thread> v;
+  ~Threads() {
+    for (auto& t : v) t.join();
+  }
+};
 }  // namespace
 
 void share_cores(const std::atomic<int>* active) { t_sharing = active; }
@@ -45,13 +53,18 @@ void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& f, int
     f(0, n);
     return;
   }
-  std::vector<std::thread> th;
+  Threads th;
+  th.v.reserve(nt);
   const int64_t c = (n + nt - 1) / nt;
-  for (int t = 0; t < nt; ++t) {
-    const int64_t a = t * c, b = std::min(n, a + c);
-    if (a < b) th.emplace_back(f, a, b);
+  for (int64_t a = 0; a < n; a += c) {
+    const int64_t b = std::min(n, a + c);
+    try {
+      th.v.emplace_back([&f, a, b] { f(a, b); });
+    } catch (const std::exception&) {   // no further thread to be had: the rest on this one
+      f(a, n);
+      return;
+    }
   }
-  for (auto& x : th) x.join();
 }
 
 Csr transpose(const Csr& M) {
@@ -218,13 +231,15 @@ Csr spgemm(const Csr& A, const Csr& B) {
   for (int i = 0; i < C.nrows; ++i) C.rp[i + 1] += C.rp[i];
   C.ci.resize(C.rp.back());
   C.v.resize(C.rp.back());
-  std::vector<std::thread> th;   // one copy per range (at most 16)
-  for (auto& kv : parts)
-    th.emplace_back([&C, &kv] {
-      std::copy(kv.second.ci.begin(), kv.second.ci.end(), C.ci.begin() + C.rp[kv.first]);
-      std::copy(kv.second.v.begin(), kv.second.v.end(), C.v.begin() + C.rp[kv.first]);
-    });
-  for (auto& t : th) t.join();
+  std::vector<const std::pair<const int64_t, Part>*> ranges;
+  for (auto& kv : parts) ranges.push_back(&kv);
+  parallel_for((int64_t)ranges.size(), [&](int64_t r0, int64_t r1) {   // a range at a time
+    for (int64_t r = r0; r < r1; ++r) {
+      const Part& part = ranges[r]->second;
+      std::copy(part.ci.begin(), part.ci.end(), C.ci.begin() + C.rp[ranges[r]->first]);
+      std::copy(part.v.begin(), part.v.end(), C.v.begin() + C.rp[ranges[r]->first]);
+    }
+  }, 1);
   return C;
 }
 

@@ -52,7 +52,8 @@ struct AmgParams {
 
 // Runs f(a, b) over [0, n) cut into contiguous ranges, on up to 16 threads
 // (one for n < 2048), and on the calling thread's share of the cores when a
-// sharing counter is set (below).  With a grain, on at most one thread per
+// sharing counter is set (below).  A thread that cannot be started leaves its
+// range and the rest to the calling one.  With a grain, on at most one thread per
 // `grain` items, however few those are: starting a thread costs as much as
 // some thousands of items of a light loop (kLight: matrix rows looked at,
 // copied or sorted).  Measured on a 15,625-row hierarchy: 11.0 -> 10.3 ms of
