@@ -10,6 +10,7 @@
 #include <cstring>
 
 #include "runtime.h"
+#include "slices.h"
 
 using namespace mmsd;
 
@@ -180,93 +181,6 @@ constexpr double kMaxFoldedBytes = 64.0 * (1 << 20);
 // in about 0.1 ms).
 constexpr int64_t kFoldGrain = 1 << 17;
 
-// A CSR matrix in slices of one wavefront, W lanes per row (1: 64 rows per
-// slice): slice s starts at so[s] and is as wide as its longest row; entry k
-// of its row r is at so[s] + 64 (k / W) + r W + k mod W; the rest is padded
-// with the row's own column (clamped to the column range) and a zero value.
-// Slices are built in parallel.
-struct Sliced {
-  std::vector<int> so, sc;
-  std::vector<double> sv;
-  std::vector<int> order;   // row at each position (empty: position = row)
-};
-
-// Rows sorted by length, longest first, inside windows of kOrderWindow rows:
-// a slice is as wide as its longest row, and the multigrid's matrices mix row
-// lengths (aggregates of 5-47 fine nodes, rows of A P next to aggregate
-// boundaries), so that sorting cuts the padding.  But neighbouring lanes then
-// hold rows further apart, whose gathers and own values share fewer cache
-// lines: with windows of 512 rows the polycrystal's post-smoothing of the
-// finest level took 84 us, with 256 82.6 us, with 128 76.8 us, within a slice
-// 77.7 us, its 14 evaluations 157.4, 155.1, 152.2 and 153.1 ms.
-constexpr int kOrderWindow = 128;
-std::vector<int> window_order(const std::vector<int>& len) {
-  const int64_t n = (int64_t)len.size();
-  std::vector<int> order(n);
-  for (int64_t i = 0; i < n; ++i) order[i] = (int)i;
-  parallel_for((n + kOrderWindow - 1) / kOrderWindow, [&](int64_t a, int64_t b) {
-    for (int64_t w = a; w < b; ++w) {
-      auto first = order.begin() + w * kOrderWindow;
-      auto last = order.begin() + std::min<int64_t>(n, (w + 1) * kOrderWindow);
-      std::stable_sort(first, last, [&](int x, int y) { return len[x] > len[y]; });
-    }
-  }, kLight / kOrderWindow);
-  return order;
-}
-// Offsets of the slices of a CSR pattern (W lanes per row).
-std::vector<int> slice_offsets(const std::vector<int>& rp, int W = 1) {
-  const int64_t n = (int64_t)rp.size() - 1, rows = 64 / W, ns = (n + rows - 1) / rows;
-  std::vector<int> so(ns + 1, 0);
-  parallel_for(ns, [&](int64_t a, int64_t b) {
-    for (int64_t sl = a; sl < b; ++sl) {
-      int w = 0;
-      for (int64_t i = rows * sl; i < std::min<int64_t>(n, rows * (sl + 1)); ++i) w = std::max(w, rp[i + 1] - rp[i]);
-      so[sl + 1] = 64 * ((w + W - 1) / W);
-    }
-  }, kLight / rows);
-  for (int64_t sl = 0; sl < ns; ++sl) so[sl + 1] += so[sl];
-  return so;
-}
-
-Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci, const std::vector<double>& v,
-                   int ncols, int W = 1, bool ordered = false) {
-  const int64_t n = (int64_t)rp.size() - 1, rows = 64 / W, ns = (n + rows - 1) / rows;
-  const int lw = std::ilogb(W);   // W is a power of two
-  Sliced S;
-  if (ordered) {
-    std::vector<int> len(n);
-    for (int64_t i = 0; i < n; ++i) len[i] = rp[i + 1] - rp[i];
-    S.order = window_order(len);
-    std::vector<int> rpo(n + 1, 0);   // row starts of the rows in position order (lengths only matter)
-    for (int64_t q = 0; q < n; ++q) rpo[q + 1] = rpo[q] + len[S.order[q]];
-    S.so = slice_offsets(rpo, W);
-  } else {
-    S.so = slice_offsets(rp, W);
-  }
-  S.sc.assign(S.so[ns], 0);
-  S.sv.assign(S.so[ns], 0.0);
-  parallel_for(ns, [&](int64_t a, int64_t b) {
-    for (int64_t sl = a; sl < b; ++sl) {
-      const int w = (S.so[sl + 1] - S.so[sl]) / 64;
-      for (int r = 0; r < rows; ++r) {
-        const int64_t pos = rows * sl + r;
-        const int64_t i = pos < n && ordered ? S.order[pos] : pos;
-        const int len = pos < n ? rp[i + 1] - rp[i] : 0;
-        for (int k = 0; k < w * W; ++k) {
-          const int64_t q = S.so[sl] + 64LL * (k >> lw) + r * W + (k & (W - 1));
-          if (k < len) {
-            S.sc[q] = ci[rp[i] + k];
-            S.sv[q] = v[rp[i] + k];
-          } else {
-            S.sc[q] = (int)std::min<int64_t>(i, ncols - 1);
-          }
-        }
-      }
-    }
-  }, kLight / rows);
-  return S;
-}
-
 // Algorithmic bytes per executed phase: every matrix entry, index and
 // row-local vector value moved once; gathered neighbour values counted as
 // cache hits.
@@ -367,9 +281,8 @@ int build_amg(mmsd_problem p) {
     for (int k = 0; k < 3; ++k) {
       if (!X[k]) continue;
       lanes[l][k] = lanes_of(*X[k]);
-      if (X[k]->ci.size() >= (size_t)1 << 29) return invalid("multigrid matrix too large to slice");
       sl[l][k] = make_sliced(X[k]->rp, X[k]->ci, X[k]->v, X[k]->ncols, lanes[l][k], /*ordered=*/true);
-      if ((int64_t)sl[l][k].so.back() >= (int64_t)1 << 30) return invalid("multigrid matrix too large to slice");
+      if (sl[l][k].so.empty()) return invalid("multigrid matrix too large for 32-bit slice offsets");
     }
   }
   // the last level's DOWN also solves the coarsest level when it restricts
