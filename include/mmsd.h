@@ -127,8 +127,11 @@ typedef struct {
  * upper bound for the first arena (operators, node state, control; exact but
  * for the potential matrix's zero couplings, which are not stored), plus an
  * allowance for the multigrid hierarchy, whose size is known only after its
- * setup ((24 + 2 s) bytes per potential-matrix entry and 8 s per potential
- * node, s = 8 for FP64, 4 for mixed). */
+ * setup: the larger of (24 + 2 s) bytes per potential-matrix entry and 8 s per
+ * potential node, and (10 + 2.5 s) per entry and 12 s per node plus the dense
+ * matrices of its coarsest level (up to 600^2 and 600 x 6000 values), s = 8 for
+ * FP64, 4 for mixed.  It covers every mesh measured (cells stretched up to 50
+ * times); a mesh whose levels coarsen by less than 4 and 5 may take more. */
 int mmsd_footprint(const mmsd_mesh* mesh, int precision, size_t* bytes_out);
 
 /* The minimization problem of the Method section, eq. (1): the total Gibbs

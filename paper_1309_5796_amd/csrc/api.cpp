@@ -991,6 +991,27 @@ void mmsd_ctx_s::dfree(void* p) {
   else (void)hipFree(p);
 }
 
+// Bytes allowed for the multigrid hierarchy's arena, which is known only after
+// its setup, from the potential matrix's sliced entries and rows.  The larger of
+//   (24 + 2 s) per entry + 8 s per row, which covers three levels and more
+//     (the 80 nm cube in FP64: 111 MB held, 164 MB allowed), and
+//   (10 + 2.5 s) per entry + 12 s per row for the sweeps' matrices and vectors,
+//     plus the dense matrices: Ainv, and Ainv M (coarsest size x last level's
+//     rows) from two levels.  They are most of a two-level hierarchy (the served
+//     box of 34,225 rows: 27.7 of 39.6 MB, for which the first term allows
+//     22.2 MB and this one 50.0).  A level is taken to coarsen by 4 at least
+//     and the next by 5 (measured: 6 and 9 on the Kuhn meshes, 14 and 12 on the
+//     Delaunay ones, 4.5 and 5.8 on cells stretched 50 times), the coarsest to
+//     hold up to AmgParams::coarse_max rows, the last level 10 times that.
+// Over 58 meshes of 729 to 1.1M rows, cells stretched up to 50 times among
+// them, the hierarchy takes 0.18 to 0.91 of it.
+static size_t hierarchy_allowance(int64_t entries, int64_t rows, size_t s) {
+  const double e = (double)entries, n = (double)rows, coarse = AmgParams{}.coarse_max, n1 = n / 4;
+  double dense = std::min(coarse, n1) * std::min(coarse, n1);
+  if (n1 > coarse) dense += std::min(coarse, n1 / 5) * std::min(10 * coarse, n1);
+  return (size_t)std::max((24 + 2.0 * s) * e + 8.0 * s * n, (10 + 2.5 * s) * e + 12.0 * s * n + s * dense);
+}
+
 // Key of the autotuner's cache: a problem class (precision, floor(log2(N + 1)),
 // floor(log2(N_t + 1))).
 static int64_t tune_key(int precision, int log2_n, int log2_nt) {
@@ -1149,11 +1170,7 @@ int mmsd_footprint(const mmsd_mesh* mesh, int precision, size_t* bytes_out) {
     return rc;
   }
   const size_t sv = precision == MMSD_MIXED ? 4 : 8;
-  // the multigrid hierarchy's arena, known only after its setup: an
-  // allowance of (24 + 2 s) bytes per potential-matrix entry and 8 s per
-  // potential node (the 80 nm cube's FP64 hierarchy, counted from its
-  // layout: ~155 MB against 166 MB allowed)
-  const size_t amg = ps.Nt > 0 ? (24 + 2 * sv) * (size_t)ps.nnzLs + 8 * sv * (size_t)ps.Nt : 0;
+  const size_t amg = ps.Nt > 0 ? hierarchy_allowance(ps.nnzLs, ps.Nt, sv) : 0;
   *bytes_out = make_layout(ps.N, ps.nnzM, ps.Nt, ps.nnzLs, sv).total + amg;
   return MMSD_OK;
 }
