@@ -222,7 +222,14 @@ typedef struct {
  * (also in out->status): MMSD_OK, MMSD_W_MAXEVALS, MMSD_W_FLOOR, or an error
  * (MMSD_E_NONFINITE when the energy or torque became non-finite; m is then
  * the last accepted state).  The potential is warm-started from the last
- * solve. */
+ * solve.
+ * The call returns when the result is there.  Up to 128 launches issued ahead
+ * may then still be queued on the context's stream: they find the run done,
+ * touch nothing, take about 2 us each, and whatever is issued on the stream
+ * afterwards (this library's own calls among it) comes after them.  A run that
+ * is not done after MMSD_RUN_TIMEOUT_S seconds of wall time (environment, default
+ * 1800) is given up with MMSD_E_HIP.  The same holds for mmsd_evaluate and each
+ * step of mmsd_hysteresis. */
 int mmsd_minimize(mmsd_problem p, const mmsd_options* o, mmsd_result* out);
 
 /* One evaluation of eq. (1) and its gradient (no step; the effective field

@@ -11,6 +11,7 @@
 
 #include "runtime.h"
 #include "slices.h"
+#include "wait.h"
 
 using namespace mmsd;
 
@@ -781,7 +782,7 @@ const Ctrl* outcome(mmsd_problem p) {
 // Launches of the next batch after `launched`.  Two batches are kept in
 // flight, so on average one and a half batches of launches find the problem
 // done (about 2 us each), while every batch costs a gap of about 7 us on the
-// stream: the batches grow as the square root of the launches so far.  A
+// stream: 8 launches, then 16 up to the 256th, 32 up to the 1,024th and 64.  A
 // small first one serves an evaluation without the stray field, which needs
 // three launches.  With batches that doubled to 64 at once and a copy of the
 // control state behind each, an evaluation of the 20 nm cube issued 248
@@ -825,12 +826,21 @@ int run_single(mmsd_problem p, const Resolved& r, int stage, int store_h, mmsd_r
       ++issued;
       continue;
     }
-    const hipError_t e = hipEventQuery(c->batch_ev[finished & 1]);
-    if (e == hipErrorNotReady) {
-      for (int k = 0; k < 16; ++k) __builtin_ia32_pause();
-      continue;
+    hipError_t e = hipSuccess;
+    const Wait w = wait_batch([&] { return outcome(p) != nullptr; },
+                              [&] {
+                                e = hipEventQuery(c->batch_ev[finished & 1]);
+                                return e == hipSuccess ? 1 : e == hipErrorNotReady ? 0 : -1;
+                              },
+                              [&] { return run_timed_out(t0); });
+    if (w == Wait::kOutcome) continue;
+    if (w == Wait::kTimeout) {
+      // what is in flight ends by itself, and all later work on the problem is
+      // ordered behind it: nothing here waits for a batch that may hang
+      set_error("run exceeded MMSD_RUN_TIMEOUT_S");
+      return MMSD_E_HIP;
     }
-    if (e != hipSuccess) {
+    if (w == Wait::kError) {
       rc = hip_fail(e, "batch wait");
       break;
     }
@@ -847,11 +857,6 @@ int run_single(mmsd_problem p, const Resolved& r, int stage, int store_h, mmsd_r
       }
     }
     ++finished;
-    if (run_timed_out(t0)) {
-      set_error("run exceeded MMSD_RUN_TIMEOUT_S");
-      rc = MMSD_E_HIP;
-      break;
-    }
   }
   if (rc) {
     (void)hipGetLastError();
