@@ -204,11 +204,20 @@ __device__ __forceinline__ void chunk_rows(int R, int G, int blk, int rpp, int a
 // non-temporal hint (nt), so that they do not push the gathered vectors and
 // the coarse levels' data out of the L2 (14 evaluations of the polycrystal
 // 169.5 ms without, 156.9 with); on smaller ones, which the Infinity Cache
-// holds, the plain loads are faster.
+// holds, the plain loads are faster.  Matrices with several lanes per row are
+// those of coarse levels, which the caches hold between the cycles: they keep
+// the plain loads (with the hint on them too, 14 evaluations of polycrystals
+// took, FP64, 1.11M rows 79.1 instead of 77.9 ms, 1.53M 104.1 / 102.5, 2.17M
+// 151.7 / 150.3; mixed, 1.53M 43.5 / 43.3, 2.17M 64.2 / 63.6).
 template <bool NT, typename T>
 __device__ __forceinline__ T stream_ld(DevPtr<const T> p, int i) {
   if constexpr (NT) return __builtin_nontemporal_load(p + i);
   else return p[i];
+}
+
+template <typename real>
+__device__ __forceinline__ bool streamed(const ProbDev<real>& P, int lw) {
+  return P.stream != 0 && lw == 0;
 }
 
 // The matrices of the potential solve are held in slices: a wavefront owns a
@@ -263,7 +272,7 @@ __device__ __forceinline__ Acc slice_row_t(DevPtr<const int> so, DevPtr<const in
   return acc;
 }
 
-// ... with the problem's load form (a uniform branch: both loops are
+// ... with the load form as an argument (a uniform branch: both loops are
 // compiled, one runs).
 template <typename real, typename Acc = real, typename G>
 __device__ __forceinline__ Acc slice_row(DevPtr<const int> so, DevPtr<const int> sc, DevPtr<const real> sv, int i,
@@ -561,7 +570,7 @@ __device__ __forceinline__ void restrict_rows(const ProbDev<real>& P, const MgLe
   const NextRhs<real> nx(P, l);
   const int lw = L.lanes_r;
   sweep(L.n_next, G, blk, lw, L.rord, [&](int i, int ri, int lane, bool valid) {
-    real sum = valid ? slice_row<real>(L.rso, L.rsc, L.rsv, i, lw, P.stream != 0, g) : real(0);
+    real sum = valid ? slice_row<real>(L.rso, L.rsc, L.rsv, i, lw, streamed(P, lw), g) : real(0);
     sum = lanes_sum(sum, lw);
     if (valid && lane == 0) {
       nx.b[ri] = sum;
@@ -579,7 +588,7 @@ __device__ __forceinline__ void down_rows(const ProbDev<real>& P, const Ctrl* C,
   DevPtr<const real> __restrict__ wb = L.wb;
   const int lw = L.lanes_a;
   sweep(L.n, G, blk, lw, L.aord, [&](int i, int ri, int lane, bool valid) {
-    real sum = valid ? slice_row<real>(L.aso, L.asc, L.asv, i, lw, P.stream != 0,
+    real sum = valid ? slice_row<real>(L.aso, L.asc, L.asv, i, lw, streamed(P, lw),
                                        [&](int j) { return l == 0 ? wd[j] * b[j] : wb[j]; })
                      : real(0);
     sum = lanes_sum(sum, lw);
@@ -598,7 +607,7 @@ __device__ __forceinline__ void post_rows(const ProbDev<real>& P, const Ctrl* C,
   DevPtr<const real> __restrict__ res = L.res;
   const int lw = L.lanes_q;
   sweep(L.n, G, blk, lw, L.qord, [&](int i, int ri, int lane, bool valid) {
-    real sum = valid ? slice_row<real>(L.qso, L.qsc, L.qsv, i, lw, P.stream != 0, [&](int j) { return y[j]; })
+    real sum = valid ? slice_row<real>(L.qso, L.qsc, L.qsv, i, lw, streamed(P, lw), [&](int j) { return y[j]; })
                      : real(0);
     sum = lanes_sum(sum, lw);
     if (valid && lane == 0) {
