@@ -294,20 +294,25 @@ Csr without_zero_couplings(const std::vector<int>& rp, const std::vector<int>& c
   Csr Z;
   Z.nrows = Z.ncols = n;
   Z.rp.assign(n + 1, 0);
+  const int64_t grain = light_rows(n, rp[n]);
   diag->assign(n, 0.0);
   std::vector<double>& d = *diag;
   parallel_for(n, [&](int64_t a, int64_t b) {
     for (int64_t i = a; i < b; ++i)
       for (int k = rp[i]; k < rp[i + 1]; ++k)
-        if (ci[k] == i) d[i] = v[k];
-  }, kLight);
-  auto kept = [&](int64_t i, int k) {
-    return ci[k] == i || !(std::fabs(v[k]) <= kZeroCoupling * std::fmin(d[i], d[ci[k]]));
+        if (ci[k] == i) {
+          d[i] = v[k];
+          break;
+        }
+  }, grain);
+  auto kept = [&](int64_t i, int k) {   // most are by the row's own diagonal, without a look at the column's
+    const double x = std::fabs(v[k]);
+    return x > kZeroCoupling * d[i] || ci[k] == i || !(x <= kZeroCoupling * std::fmin(d[i], d[ci[k]]));
   };
   parallel_for(n, [&](int64_t a, int64_t b) {
     for (int64_t i = a; i < b; ++i)
       for (int k = rp[i]; k < rp[i + 1]; ++k) Z.rp[i + 1] += kept(i, k);
-  }, kLight);
+  }, grain);
   for (int i = 0; i < n; ++i) Z.rp[i + 1] += Z.rp[i];
   Z.ci.resize(Z.rp[n]);
   Z.v.resize(Z.rp[n]);
@@ -320,7 +325,7 @@ Csr without_zero_couplings(const std::vector<int>& rp, const std::vector<int>& c
           Z.v[o++] = v[k];
         }
     }
-  }, kLight);
+  }, grain);
   return Z;
 }
 
@@ -348,15 +353,16 @@ Csr smoothed_prolongation(const AmgLevel& L) {
     }
     return o;
   };
+  const int64_t grain = light_rows(T.nrows, (int64_t)L.AP.ci.size());
   parallel_for(T.nrows, [&](int64_t a, int64_t b) {
     for (int64_t i = a; i < b; ++i) T.rp[i + 1] = merge((int)i, nullptr, nullptr);
-  }, kLight);
+  }, grain);
   for (int i = 0; i < T.nrows; ++i) T.rp[i + 1] += T.rp[i];
   T.ci.resize(T.rp[T.nrows]);
   T.v.resize(T.rp[T.nrows]);
   parallel_for(T.nrows, [&](int64_t a, int64_t b) {
     for (int64_t i = a; i < b; ++i) merge((int)i, &T.ci[T.rp[i]], &T.v[T.rp[i]]);
-  }, kLight);
+  }, grain);
   return T;
 }
 
@@ -384,7 +390,7 @@ Csr fused_post_smoothing(const AmgLevel& L, const Csr& T) {
         C.v[o] = T.v[k];
       }
     }
-  }, kLight);
+  }, light_rows(n, C.rp[n]));
   return C;
 }
 

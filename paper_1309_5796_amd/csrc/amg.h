@@ -3,6 +3,7 @@
 // `smooth_levels` levels, plain aggregation below), Galerkin coarse
 // operators, dense inverse on the coarsest level.
 #pragma once
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <functional>
@@ -55,10 +56,17 @@ struct AmgParams {
 // sharing counter is set (below).  A thread that cannot be started leaves its
 // range and the rest to the calling one.  With a grain, on at most one thread per
 // `grain` items, however few those are: starting a thread costs as much as
-// some thousands of items of a light loop (kLight: matrix rows looked at,
-// copied or sorted).  Measured on a 15,625-row hierarchy: 11.0 -> 10.3 ms of
-// device setup.
-constexpr int64_t kLight = 8192;
+// some ten thousands of entries of a light loop (matrix rows looked at, copied or
+// sorted).  light_rows is the grain of such a loop over the rows of a matrix
+// with `entries` entries: by entries, since rows hold 7 (a Kuhn mesh's potential
+// matrix) to 50 of them (the fused post-smoothing of a Delaunay mesh, whose
+// slices were filled in 5.7 ms with a grain of 8,192 rows and 64-bit zeros
+// written first, and are in 2.9 ms).  kLight: the grain of loops over row lengths
+// alone.
+constexpr int64_t kLight = 8192, kLightEntries = 65536;
+inline int64_t light_rows(int64_t rows, int64_t entries) {
+  return std::max<int64_t>(1, rows * kLightEntries / std::max<int64_t>(1, entries));
+}
 void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& f, int64_t grain = 0);
 
 // Threads that share the cores: while `active` is set on a thread, its

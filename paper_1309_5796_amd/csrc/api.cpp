@@ -94,8 +94,8 @@ Layout make_layout(int64_t N, int64_t nnzM, int64_t Nt, int64_t nnzLs, size_t s)
   return L;
 }
 
-template <typename real>
-int upload_vec(hipStream_t st, char* dst, const std::vector<double>& v) {
+template <typename real, typename Alloc>
+int upload_vec(hipStream_t st, char* dst, const std::vector<double, Alloc>& v) {
   if (v.empty()) return MMSD_OK;
   if constexpr (sizeof(real) == sizeof(double)) {
     MMSD_HIP(hipMemcpyAsync(dst, v.data(), v.size() * sizeof(double), hipMemcpyHostToDevice, st));
@@ -108,7 +108,8 @@ int upload_vec(hipStream_t st, char* dst, const std::vector<double>& v) {
   return MMSD_OK;
 }
 
-int upload_int(hipStream_t st, char* dst, const std::vector<int>& v) {
+template <typename Alloc>
+int upload_int(hipStream_t st, char* dst, const std::vector<int, Alloc>& v) {
   if (v.empty()) return MMSD_OK;
   MMSD_HIP(hipMemcpyAsync(dst, v.data(), v.size() * sizeof(int), hipMemcpyHostToDevice, st));
   MMSD_HIP(hipStreamSynchronize(st));
@@ -434,7 +435,8 @@ int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
   mmsd_ctx c = p->ctx;
   const Assembly& A = p->A;
   const int64_t N = A.N, Nt = A.Nt, nnzM = (int64_t)A.mci.size();
-  const int64_t nnzLs = Nt ? sliced_entries(p->L.rp) : 0;
+  const Csr& Lm = p->has_amg ? p->amg.lv[0].A : p->L;   // the potential matrix without zero couplings
+  const int64_t nnzLs = Nt ? sliced_entries(Lm.rp) : 0;
   if (nnzLs >= (int64_t)1 << 31) return invalid("potential matrix too large for 32-bit slice offsets");
   p->lpr = c->lpr;
   p->G = blocks_for(std::max<int64_t>(N, Nt), p->lpr, c->max_blocks);
@@ -484,7 +486,7 @@ int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
       return MMSD_E_NOMEM;
     }
     D->owned.push_back(diag);
-    if ((rc = upload_int(st, base + L.lso, slice_offsets(p->L.rp))) ||
+    if ((rc = upload_int(st, base + L.lso, slice_offsets(Lm.rp))) ||
         (rc = upload_vec<double>(st, (char*)diag, p->Ldiag)))
       return rc;
     MMSD_HIP(launch_slice_rows<real>(D->lrp, D->lci, D->L, diag, (const int32_t*)(base + L.lso), Nt,
@@ -492,7 +494,7 @@ int build_device(mmsd_problem p, DeviceAssembly* D = nullptr) {
                                      (real*)(base + L.rec[0]), (real*)(base + L.rec[1]), st));
   } else if (Nt > 0) {
     // the potential matrix lives on the device only in its sliced layout
-    const Sliced S = make_sliced(p->L.rp, p->L.ci, p->L.v, (int)Nt);
+    const Sliced S = make_sliced(Lm.rp, Lm.ci, Lm.v, (int)Nt);
     if ((rc = upload_int(st, base + L.lso, S.so)) || (rc = upload_int(st, base + L.lsc, S.sc)) ||
         (rc = upload_vec<real>(st, base + L.lsv, S.sv)))
       return rc;
@@ -1205,9 +1207,12 @@ int mmsd_problem_create(mmsd_ctx c, const mmsd_mesh* mesh, const mmsd_material* 
   }
   const auto t1 = Clock::now();
   if (p->A.Nt > 0) {
-    p->L = without_zero_couplings(p->A.lrp, p->A.lci, p->A.L, &p->Ldiag);
-    p->nnzL = (int64_t)p->L.ci.size();
-    p->has_amg = amg_setup(p->L, AmgParams{}, &p->amg) && (int)p->amg.lv.size() <= kMaxLevels;
+    // the matrix becomes the hierarchy's level 0 (kept by itself only without one)
+    auto potential = [&] { return without_zero_couplings(p->A.lrp, p->A.lci, p->A.L, &p->Ldiag); };
+    Csr L = potential();
+    p->nnzL = (int64_t)L.ci.size();
+    p->has_amg = amg_setup(std::move(L), AmgParams{}, &p->amg) && (int)p->amg.lv.size() <= kMaxLevels;
+    if (!p->has_amg) p->L = potential();
     // the level operators are kept only for sizes and byte counts
   }
   const auto t2 = Clock::now();

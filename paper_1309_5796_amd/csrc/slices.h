@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 #include "amg.h"
@@ -14,10 +15,21 @@ namespace mmsd {
 // slice): slice s starts at so[s] and is as wide as its longest row; entry k
 // of its row r is at so[s] + 64 (k / W) + r W + k mod W; the rest is padded
 // with the row's own column (clamped to the column range) and a zero value.
-// Slices are built in parallel.
+// Slices are built in parallel, and each value is written once: the arrays
+// start without one, so that their pages are first touched by those threads.
+template <typename T>
+struct Unset : std::allocator<T> {
+  template <typename U>
+  struct rebind {
+    using other = Unset<U>;
+  };
+  template <typename U>
+  void construct(U*) noexcept {}
+};
 struct Sliced {
-  std::vector<int> so, sc;
-  std::vector<double> sv;
+  std::vector<int> so;
+  std::vector<int, Unset<int>> sc;
+  std::vector<double, Unset<double>> sv;
   std::vector<int> order;   // row at each position (empty: position = row)
 };
 
@@ -55,7 +67,7 @@ inline std::vector<int> slice_offsets(const std::vector<int>& rp, int W = 1) {
       for (int64_t i = rows * sl; i < std::min<int64_t>(n, rows * (sl + 1)); ++i) w = std::max(w, rp[i + 1] - rp[i]);
       so[sl + 1] = (w + W - 1) / W;
     }
-  }, kLight / rows);
+  }, light_rows(ns, rp[n]));
   int64_t total = 0;
   for (int64_t sl = 1; sl <= ns; ++sl) {
     total += 64LL * so[sl];
@@ -81,8 +93,8 @@ inline Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci
     S.so = slice_offsets(rp, W);
   }
   if (S.so.empty()) return S;   // too large
-  S.sc.assign(S.so[ns], 0);
-  S.sv.assign(S.so[ns], 0.0);
+  S.sc.resize(S.so[ns]);
+  S.sv.resize(S.so[ns]);
   parallel_for(ns, [&](int64_t a, int64_t b) {
     for (int64_t sl = a; sl < b; ++sl) {
       const int w = (S.so[sl + 1] - S.so[sl]) / 64;
@@ -97,11 +109,12 @@ inline Sliced make_sliced(const std::vector<int>& rp, const std::vector<int>& ci
             S.sv[q] = v[rp[i] + k];
           } else {
             S.sc[q] = (int)std::min<int64_t>(i, ncols - 1);
+            S.sv[q] = 0.0;
           }
         }
       }
     }
-  }, kLight / rows);
+  }, light_rows(ns, rp[n]));
   return S;
 }
 
