@@ -67,6 +67,8 @@ void parallel_for(int64_t n, const std::function<void(int64_t, int64_t)>& f, int
   }
 }
 
+namespace {
+
 Csr transpose(const Csr& M) {
   Csr T;
   T.nrows = M.ncols;
@@ -85,8 +87,6 @@ Csr transpose(const Csr& M) {
     }
   return T;   // rows come out with ascending columns
 }
-
-namespace {
 
 std::vector<double> diagonal(const Csr& A) {
   std::vector<double> d(A.nrows, 0.0);
@@ -366,7 +366,7 @@ Csr smoothed_prolongation(const AmgLevel& L) {
   return T;
 }
 
-Csr residual_restriction(const AmgLevel& L) { return transpose(smoothed_prolongation(L)); }
+Csr residual_restriction(const AmgLevel& L, const Csr* T) { return transpose(T ? *T : smoothed_prolongation(L)); }
 
 Csr fused_post_smoothing(const AmgLevel& L, const Csr& T) {
   const int n = L.A.nrows;

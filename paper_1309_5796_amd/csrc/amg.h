@@ -100,11 +100,9 @@ Csr smoothed_prolongation(const AmgLevel& L);
 
 // M = R (I - A W), W = wsmooth D^-1: the restriction of the residual left by
 // one damped-Jacobi sweep from zero, b_{l+1} = M b_l.  For symmetric A it is
-// the transpose of T = (I - W A) P; rows with ascending columns.
-Csr residual_restriction(const AmgLevel& L);
-
-// The transpose, rows with ascending columns.
-Csr transpose(const Csr& M);
+// the transpose of T = (I - W A) P (given, or formed); rows with ascending
+// columns.
+Csr residual_restriction(const AmgLevel& L, const Csr* T = nullptr);
 
 // [2 I - W A | T] (T the smoothed_prolongation): the pre-smoothing, its
 // residual and the post-smoothing in one matrix over [W b | x_{l+1}], since

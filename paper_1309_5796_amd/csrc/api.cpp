@@ -274,7 +274,7 @@ int build_amg(mmsd_problem p) {
     fused[l] = (c->vcycle & MMSD_VC_FUSE_REST) &&
                fuse_restriction(L.A.nrows, L.P.ncols, L.P.ci.size() / nn, Q.ci.size() / nn, s, l == 0);
     if (fused[l]) {
-      M = transpose(Q);   // residual_restriction(L)
+      M = residual_restriction(L, &Q);
       Q = fused_post_smoothing(L, Q);
       p->amg_m_nnz[l] = (int64_t)M.ci.size();
     }
