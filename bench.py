@@ -100,12 +100,36 @@ def measured_traffic(name: str):
     return rec["traffic_bytes_per_launch"] if rec.get("kernel_source_sha256") == kernel_source_hash() else None
 
 
+def stored_potential_entries(mesh) -> int:
+    """Entries of the potential matrix that the device holds and every sweep
+    reads: couplings with |a_ij| <= 2^-52 min(a_ii, a_jj) are not stored (about
+    half of those of a box cut into Kuhn tetrahedra)."""
+    import numpy as np
+
+    from paper_1309_5796_amd import binding
+    a = binding.assembly_export(mesh)
+    row = np.repeat(np.arange(a["Nt"]), np.diff(a["lrp"]))
+    d = np.zeros(a["Nt"])
+    own = row == a["lci"]
+    d[row[own]] = a["L"][own]
+    return int((own | ~(np.abs(a["L"]) <= 2.0 ** -52 * np.minimum(d[row], d[a["lci"]]))).sum())
+
+
+def stored_sizes(p, cfg: dict) -> dict:
+    """Problem.sizes with the potential matrix's stored entries (counted once
+    per workload)."""
+    if "stored_potential_entries" not in cfg:
+        cfg["stored_potential_entries"] = stored_potential_entries(cfg["mesh"])
+    return dict(p.sizes(), nnz_potential=cfg["stored_potential_entries"])
+
+
 def bytes_per_evaluation_model(sz: dict, evals: int, pcg_iters: int, fp64: bool = True) -> float:
     """Algorithmic HBM bytes of `evals` energy-gradient evaluations with
     `pcg_iters` potential-solver iterations in all, by the per-row model of
     the method's kernels (every matrix and vector touched once, gathered
     neighbours cached; int32 indices; z, z_L the measured average row
-    lengths of the magnet pattern and of the potential matrix):
+    lengths of the magnet pattern and of the potential matrix as the device
+    holds it, see stored_potential_entries):
       FP64: per magnet node 296 + 64 z (divergence 36 + 28 z, field
             188 + 36 z, Cayley update 72); per potential row 44 + 12 z_L for
             the solve's start and 108 + 12 z_L per CG iteration;
@@ -165,7 +189,7 @@ def poly_run(ctx, cfg, prec, max_evals):
     t0 = time.perf_counter()
     p = binding.Problem(ctx, cfg["mesh"], precision=prec)
     setup = time.perf_counter() - t0
-    sz = p.sizes()
+    sz = stored_sizes(p, cfg)
     p.set_m(cfg["m0"])
     p.set_field(cfg["b_ext"])
     ctx.timing(True)
@@ -565,7 +589,7 @@ def run_sweep(args):
     if args.vcycle == "plain":
         ctx.set_vcycle(0)
     p = binding.Problem(ctx, cfg["mesh"], precision=binding.FP64)
-    sz = p.sizes()
+    sz = stored_sizes(p, cfg)
     state0 = p.get_state()
     pc = {"auto": binding.PRECOND_AUTO, "jacobi": binding.PRECOND_JACOBI, "amg": binding.PRECOND_AMG}[args.precond]
     if args.warmup > 0:
@@ -604,7 +628,7 @@ def run_sweep(args):
         roof = roofline_of(tm, f"k_step<double,{args.lanes or 4}>", sz, evals, pcg, True,
                            measured_traffic("k_step_fp64_sweep80"))
         if roof:
-            roof["memory_level"] = ("hbm-or-mall: the cube's working set (~290 MB with the multigrid hierarchy) "
+            roof["memory_level"] = ("hbm-or-mall: the cube's working set (~240 MB with the multigrid hierarchy) "
                                     "is largely resident in the 256 MB Infinity Cache")
     b0, b1 = float(bu[0]), float(bu[npts - 1])
     desc = "whole loop" if npts == len(fields) else f"first {npts} of the {len(fields)}-point loop"
