@@ -1478,6 +1478,11 @@ int mmsd_minimize_batch(mmsd_problem* probs, int n, const mmsd_options* o, mmsd_
   int* dlist = (int*)(misc + 256);
   char* tab = nullptr;
   std::vector<Table> tabs;
+  // the host sources of the table copies live until the stream is synchronized
+  // (before a rebuild and at the end): an asynchronous copy may read them
+  // after the call
+  std::vector<unsigned char> hq[2];
+  std::vector<int> bq[2];
   // One table per precision over the unfinished problems; finished ones are
   // dropped when the table is rebuilt (problems keep their block counts).
   auto build_tables = [&](const std::vector<char>& done) -> int {
@@ -1495,8 +1500,10 @@ int mmsd_minimize_batch(mmsd_problem* probs, int n, const mmsd_options* o, mmsd_
     for (int q = 0; q < 2; ++q) {
       if (idx[q].empty()) continue;
       const size_t ps = q ? sizeof(Prob<float>) : sizeof(Prob<double>);
-      std::vector<unsigned char> h(ps * idx[q].size());
-      std::vector<int> blk(idx[q].size() + 1, 0);
+      std::vector<unsigned char>& h = hq[q];
+      std::vector<int>& blk = bq[q];
+      h.assign(ps * idx[q].size(), 0);
+      blk.assign(idx[q].size() + 1, 0);
       const int lpr = probs[idx[q][0]]->lpr;
       for (size_t k = 0; k < idx[q].size(); ++k) {
         const int i = idx[q][k];
@@ -1592,8 +1599,8 @@ int mmsd_minimize_batch(mmsd_problem* probs, int n, const mmsd_options* o, mmsd_
       cur ^= 1;
       B = std::min(B * 2, 64);
     }
-    (void)hipStreamSynchronize(st);
   }
+  (void)hipStreamSynchronize(st);   // the scratch, the tables and their host sources go below
   for (hipEvent_t e : ev)
     if (e) (void)hipEventDestroy(e);
   for (auto& kv : graphs) (void)hipGraphExecDestroy(kv.second);
