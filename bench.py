@@ -81,7 +81,8 @@ def kernel_source_hash() -> str:
     import re
     h = hashlib.sha256()
     for f in ("paper_1309_5796_amd/csrc/kernels.hip", "paper_1309_5796_amd/csrc/device.h",
-              "paper_1309_5796_amd/csrc/api.cpp", "paper_1309_5796_amd/csrc/amg.cpp"):
+              "paper_1309_5796_amd/csrc/api.cpp", "paper_1309_5796_amd/csrc/amg.cpp",
+              "paper_1309_5796_amd/csrc/slices.h"):
         with open(os.path.join(ROOT, f), encoding="utf-8") as fh:
             text = re.sub(r"/\*.*?\*/", "", fh.read(), flags=re.S)
         lines = (re.sub(r"//.*$", "", ln).rstrip() for ln in text.splitlines())

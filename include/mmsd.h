@@ -159,8 +159,8 @@ int mmsd_n_magnetic(mmsd_problem p, int64_t* n);   /* N: magnetic nodes */
 int mmsd_n_potential(mmsd_problem p, int64_t* n);  /* free (non-Dirichlet) nodes, 0 if none */
 /* Operator sizes: sizes[4] = {N, entries of the magnet-row pattern (shared by
  * the exchange and the two gradient operators), N_t, entries of the
- * potential matrix (CSR, before any padding)}.  The measurement of the
- * algorithmic bytes per evaluation uses the average row lengths. */
+ * assembled potential matrix (CSR, before any padding; the device does not
+ * store its zero couplings)}. */
 int mmsd_problem_sizes(mmsd_problem p, int64_t sizes[4]);
 
 /* Material constants of the exchange and anisotropy terms of eq. (1) for one

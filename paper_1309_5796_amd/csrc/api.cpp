@@ -1,8 +1,8 @@
 // C ABI of the minimizer: contexts, problem upload, device-driven
 // minimization runs, hysteresis continuation, batched runs, checkpoints and
 // kernel timing.  All device work goes through the step kernel; the host
-// only arms a run and polls a small control block (one batch of launches of
-// lookahead), so no host round trip sits between phases.
+// only arms a run, keeps two batches of launches in flight and waits for the
+// outcome in pinned memory, so no host round trip sits between phases.
 #include <algorithm>
 #include <array>
 #include <cmath>
@@ -128,7 +128,8 @@ static int64_t sweep_passes(int64_t n, int64_t g, int W) {
 }
 
 // Latency cost of a sweep of n rows of avg entries at W lanes per row over a
-// full launch's 512 blocks, in units of one dependent round trip: each block
+// full launch's 512 blocks (a batch or another launch shape gives a problem
+// other counts, but its matrices are laid out once), in units of one dependent round trip: each block
 // pass loads the slice's offset, then per batch the entries and their gathers
 // (8 steps per batch), then stores.
 static int64_t sweep_cost(int64_t n, double avg, int W) {
@@ -160,12 +161,18 @@ static int row_lanes(int64_t n, double avg) {
 // is the larger of its round trips over a full launch's 512 blocks and its
 // bytes, entries and gathers, a round trip being worth about 3.5 MB at the
 // rate a sweep of large matrices reaches.  On the finest level M's rows gather
-// scattered {r, q} records, counted as 8 values each, which draws the line
-// near 20,000 rows: with M the 20 nm cube's iteration loses one of six
-// launches (evaluation 1.18 -> 1.08 ms); the 132,651-row ball alone would
-// still gain 2% (16 evaluations 19.65 -> 19.2 ms), but 14 grains of 13k to
-// 110k rows in one batch lose 6% (60.6 -> 64.3 ms), and the 80 nm cube's
-// iteration grows from 67.1 to 70.0 us (PCG_B with M 18.5 us against
+// scattered {r, q} records, counted as 8 values each: fitted in FP64, where it
+// draws the line between 19,683 and 22,869 rows; its bytes scale with the value
+// size, so the mixed form's lies between 39,304 and 42,875.
+// Neither is where one kind of run alone would have it: with M a problem alone
+// loses one of six launches and gains on either side of the lines, and a batch,
+// whose launches are full, loses on either side.  12 evaluations with / without
+// M on the finest level, FP64: alone 19,683 rows 6.1 / 6.6 ms, 24,389 7.2 / 7.7,
+// 35,937 9.2 / 9.8, 46,656 10.8 / 11.2; 14 cubes of 22k to 39k rows in a batch
+// 38.7 / 37.3, of 32k to 39k 39.6 / 37.4.  Mixed: alone 19,683 rows 2.9 / 3.1,
+// 24,389 3.1 / 3.3, 35,937 4.2 / 4.4, 39,304 4.1 / 4.5, 46,656 4.6 / 4.9; the
+// batches 13.4 / 13.2 and 14.5 / 13.9.  Far above them both lose: the 80 nm
+// cube's iteration grows from 67.1 to 70.0 us (PCG_B with M 18.5 us against
 // 10.1 + 9.0 us for PCG_B and REST, POST with A 14.0 against 11.1 us).
 constexpr double kTripBytes = 3.5e6;
 static bool fuse_restriction(int64_t n, int64_t nR, double avgR, double avgM, size_t s, bool finest) {
